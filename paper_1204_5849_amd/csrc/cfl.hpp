@@ -6,6 +6,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include "fp64.hpp"
 #include "map_internal.hpp"
 
 namespace mapk {
@@ -20,7 +21,7 @@ __device__ __forceinline__ double cfl_speed(const double (&u)[NV], double gamma,
     // the same arithmetic in every translation unit that includes this
 #pragma clang fp contract(off)
     // primitives once per cell, then |v_d| + c_f,d for each d
-    const double ir = 1.0 / u[RHO];
+    const double ir = rcp64(u[RHO]);
     const double vx = u[MX] * ir, vy = u[MY] * ir, vz = u[MZ] * ir;
     const double ke = 0.5 * (u[MX] * vx + u[MY] * vy + u[MZ] * vz);
     const double bb = u[BX] * u[BX] + u[BY] * u[BY] + u[BZ] * u[BZ];
@@ -30,9 +31,9 @@ __device__ __forceinline__ double cfl_speed(const double (&u)[NV], double gamma,
     auto fast = [&](double vd, double Bd) {
         double disc = sab * sab - 4.0 * a2 * (Bd * Bd) * ir;
         disc = disc < 0.0 ? 0.0 : disc;
-        double cf2 = 0.5 * (sab + sqrt(disc));
+        double cf2 = 0.5 * (sab + sqrt64(disc));
         cf2 = cf2 < 0.0 ? 0.0 : cf2;
-        return fabs(vd) + sqrt(cf2);
+        return fabs(vd) + sqrt64(cf2);
     };
     double s = fast(vx, u[BX]);
     const double s1 = fast(vy, u[BY]);

@@ -8,6 +8,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include "fp64.hpp"
 #include "map_internal.hpp"
 
 namespace mapk {
@@ -17,9 +18,9 @@ struct Num;
 
 template <>
 struct Num<double> {
-    static __device__ __forceinline__ double rcp(double x) { return 1.0 / x; }
-    static __device__ __forceinline__ double sqrt_(double x) { return sqrt(x); }
-    static __device__ __forceinline__ double div(double a, double b) { return a / b; }
+    static __device__ __forceinline__ double rcp(double x) { return rcp64(x); }
+    static __device__ __forceinline__ double sqrt_(double x) { return sqrt64(x); }
+    static __device__ __forceinline__ double div(double a, double b) { return div64(a, b); }
 };
 
 template <>
