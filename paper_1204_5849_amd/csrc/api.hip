@@ -247,6 +247,25 @@ map_status run_cfl_rest(map_ctx *c, const void *U, hipStream_t s, map_dt *dt_int
     return run_dt(c, nullptr, s, dt_int);
 }
 
+// row segments per group of blocks of the 2-D LF and WENO updates: the most
+// with which every work item is resident at once, at one wave per SIMD in FP64
+// and two in FP32 (the registers of the instances).  A segment of 16 / 2^l
+// rows passes over two more, so splitting further only adds work.  us per cycle
+// on n x n blocks, FP64 LF with at most 1, 2 and 4 seven-block items per CU:
+// n = 16 32.9 / 32.6 / 41.5, n = 24 44.4 / 44.2 / 54.2; FP32 LF with 1, 2, 4:
+// n = 16 31.2 / 28.1 / 25.5, n = 24 44.2 / 38.0 / 31.8, FP32 WENO n = 52
+// 186 / 186 / 125.  The CFL maxima that a fused update forms need whole blocks.
+int step_lseg(const map_ctx *c, int ngroups, bool cfl_on)
+{
+    if (c->nd != 2 || c->p.scheme == MAP_MMC || cfl_on)
+        return 0;
+    const int waves = c->step_shape == 1 ? 2 : 4, room = c->ncu * (fp64(c) ? 4 : 8);
+    int l = 0;
+    while ((1 << l) < NB && ((long long)ngroups << (l + 1)) * waves <= room)
+        l++;
+    return l;
+}
+
 // one launch of the block-update kernel of the scheme (for WENO: one stage)
 map_status run_step_kernel(map_ctx *c, int sch, const void *Uin, void *Uout, const void *Ubase,
                            const map_dt *dt, hipStream_t s, bool cfl_next = false)
@@ -284,13 +303,16 @@ map_status run_step_kernel(map_ctx *c, int sch, const void *Uin, void *Uout, con
         for (int i = 0; i < c->nleaves; i++) {
             a.leaves = dptr<int32_t>(c, c->ws.leaves) + i;
             a.nleaves = 1;
-            a.nitems = 1;
-            HIPCHK(launch(a, 1));
+            a.lseg = step_lseg(c, 1, a.cfl_on);
+            a.nitems = 1 << a.lseg;
+            HIPCHK(launch(a, 0));
         }
     } else {
         a.leaves = dptr<int32_t>(c, c->ws.leaves);
         a.nleaves = c->nleaves;
-        a.nitems = (c->nleaves + bpw - 1) / bpw;
+        const int groups = (c->nleaves + bpw - 1) / bpw;
+        a.lseg = step_lseg(c, groups, a.cfl_on);
+        a.nitems = groups << a.lseg;
         HIPCHK(launch(a, c->grid_step));
     }
     return MAP_OK;

@@ -29,6 +29,13 @@
 //     read from U_base at the cell itself, damps psi, and averages the reflux
 //     face fluxes of both stages.
 // A persistent grid strides over the leaf list.
+//
+// A tree too small to fill the chip is split along the march as well: a work
+// item updates the rows [k0, k1) of its group's blocks, starting one row below
+// (2^lseg items per group).  The march is one long dependent chain, about 4.7 us
+// a row in FP64 at one wave per SIMD, so on an idle chip the rows of a block go
+// to different CUs at the price of two more row passes per item: 128^2
+// Orszag-Tang, 10 -> 160 workgroups, 80 -> 17 us per update.
 #include <type_traits>
 
 #include "cfl.hpp"
@@ -119,10 +126,13 @@ __global__ void __launch_bounds__(nt_of(BPW), occ_hint<T>(BPW)) k_step2(StepArgs
     int first, stride, end;
     xcd_range(a.nitems, first, stride, end);
     for (int item = first; item < end; item += stride) {
-        const int li = item * BPW + lb;
+        // the rows [k0, k1) of the group's blocks that this item updates
+        const int grp = item >> a.lseg;
+        const int nrow = NB >> a.lseg, k0 = (item - (grp << a.lseg)) * nrow, k1 = k0 + nrow;
+        const int li = grp * BPW + lb;
         const bool has = lane && li < a.nleaves;
         const int slot = has ? a.leaves[li] : 0;
-        const int lix = item * BPW + xlb;
+        const int lix = grp * BPW + xlb;
         const bool xhas = xq >= 0 && lix < a.nleaves;
         const int xslot = xhas ? a.leaves[lix] : 0;
         const BlockRec br = a.blk[slot];
@@ -195,22 +205,23 @@ __global__ void __launch_bounds__(nt_of(BPW), occ_hint<T>(BPW)) k_step2(StepArgs
 
         T u0[NV], up[NV], upp[NV], xc[NV];
         {
-            // row -2 of the own column: read back as the k-1 row at k = -1
+            // row k0-2 of the own column: read back as the k-1 row at k = k0-1
             T um[NV];
-            load(um, -2);
+            load(um, k0 - 2);
+            T *const s = su + (k0 & 1) * SUB;
             if (lane) {
 #pragma unroll
                 for (int v = 0; v < NV; v++)
-                    su[(lb * NV + v) * XS + q] = um[v];
+                    s[(lb * NV + v) * XS + q] = um[v];
             }
         }
-        load(u0, -1);
-        load(up, 0);
-        load_x(xc, -1);
+        load(u0, k0 - 1);
+        load(up, k0);
+        load_x(xc, k0 - 1);
         if constexpr (TWOB) {
-            // LF: row -1 in LDS before the march, the load-only cell of row 0
-            // in flight
-            T *const s = su + SUB;  // row -1
+            // LF: row k0-1 in LDS before the march, the load-only cell of row
+            // k0 in flight
+            T *const s = su + ((k0 + 1) & 1) * SUB;  // row k0-1
             if (lane) {
 #pragma unroll
                 for (int v = 0; v < NV; v++)
@@ -221,7 +232,7 @@ __global__ void __launch_bounds__(nt_of(BPW), occ_hint<T>(BPW)) k_step2(StepArgs
                 for (int v = 0; v < NV; v++)
                     s[(xlb * NV + v) * XS + xq] = xc[v];
             }
-            load_x(xc, 0);
+            load_x(xc, k0);
             __syncthreads();
         }
         // carried to the next row: Wc = u - (x flux difference) + dt (sources
@@ -243,8 +254,11 @@ __global__ void __launch_bounds__(nt_of(BPW), occ_hint<T>(BPW)) k_step2(StepArgs
             jm2[i] = T(0);
         }
 
-        for (int k = -1; k <= NB; ++k) {
-            const bool kI = k >= 0 && k < NB;
+        for (int k = k0 - 1; k <= k1; ++k) {
+            const bool kI = k >= k0 && k < k1;
+            // counters: a row's fall-backs by the segment that updates it
+            // (rows -1 and NB by the first and the last)
+            const bool kcnt = kI || k < 0 || k >= NB;
             T *const sc = su + ((k + 2) & 1) * SUB;  // row k
             T *const sm = su + ((k + 1) & 1) * SUB;  // row k-1
             auto um = [&](int v) { return sm[(lb * NV + v) * XS + q]; };
@@ -253,7 +267,7 @@ __global__ void __launch_bounds__(nt_of(BPW), occ_hint<T>(BPW)) k_step2(StepArgs
             if constexpr (TWOB) {
                 // row k is in LDS (published before the previous row's last
                 // barrier); prefetch the own column's row k+2
-                if (k + 2 <= NB + 1)
+                if (k + 2 <= k1 + 1)
                     load(upp, k + 2);
             } else {
                 // ---- (A) publish row k (own column and the load-only cell)
@@ -267,12 +281,12 @@ __global__ void __launch_bounds__(nt_of(BPW), occ_hint<T>(BPW)) k_step2(StepArgs
                     for (int v = 0; v < NV; v++)
                         sc[(xlb * NV + v) * XS + xq] = xc[v];
                 }
-                if (k + 2 <= NB + 1)
+                if (k + 2 <= k1 + 1)
                     load(upp, k + 2);
-                if (k + 1 <= NB + 1)
+                if (k + 1 <= k1 + 1)
                     load_x(xc, k + 1);
                 if constexpr (SCH == SCH_WENO2) {
-                    if (inI && k >= 1 && has) {
+                    if (inI && k > k0 && has) {
                         const T *b = (const T *)a.Ubase + (size_t)slot * NV * P + (k - 1 + NG) * XS + q;
 #pragma unroll
                         for (int v = 0; v < NV; v++)
@@ -286,7 +300,7 @@ __global__ void __launch_bounds__(nt_of(BPW), occ_hint<T>(BPW)) k_step2(StepArgs
             T pLm = T(1), pRm = T(1);
             T src[4] = {T(0), T(0), T(0), T(0)};
             T jc[3] = {T(0), T(0), T(0)};
-            // rows -1 and NB only feed the faces between rows: interior columns
+            // rows k0-1 and k1 only feed the faces between rows: interior columns
             const bool work = lane && (kI || inI);
             if (work) {
                 // slopes from the old-time differences (limiter1)
@@ -338,7 +352,7 @@ __global__ void __launch_bounds__(nt_of(BPW), occ_hint<T>(BPW)) k_step2(StepArgs
 #pragma unroll
                         for (int v = 0; v < NV; v++)
                             acc[v] = T(0);
-                        if (has)
+                        if (has && kcnt)
                             atomicAdd(&a.cnt[0], 1ull);
                     }
 #pragma unroll
@@ -371,7 +385,7 @@ __global__ void __launch_bounds__(nt_of(BPW), occ_hint<T>(BPW)) k_step2(StepArgs
                     prim_of(ph, L, wl);
                     prim_of(ph, R, wr);
                     // count a replaced state once, for faces of interior cells
-                    const bool others = qc[1 - d] >= 0 && qc[1 - d] < NB;
+                    const bool others = kcnt && qc[1 - d] >= 0 && qc[1 - d] < NB;
                     if (!admissible_w(L, wl)) {
 #pragma unroll
                         for (int v = 0; v < NV; v++)
@@ -408,7 +422,7 @@ __global__ void __launch_bounds__(nt_of(BPW), occ_hint<T>(BPW)) k_step2(StepArgs
                 }
                 // the flux of the face k-1/2 from registers only, formed
                 // before the barriers so that its states die early
-                if (inI && k >= 0)
+                if (inI && k >= k0)
                     face_flux<RS, 1>(Lm_prev, pLm_prev, Rm, pRm, gam, ph.gm1, ch, ch2, fmc);
                 // EGLM sources from central differences of u^n
                 if (a.eglm && inI && kI) {
@@ -451,7 +465,7 @@ __global__ void __launch_bounds__(nt_of(BPW), occ_hint<T>(BPW)) k_step2(StepArgs
             //      readers are behind (B); the barrier (D) below orders it
             //      before row k+1's pass.  Prefetch the load-only cell of
             //      row k+2.
-            if (TWOB && k + 1 <= NB) {
+            if (TWOB && k + 1 <= k1) {
                 if (lane) {
 #pragma unroll
                     for (int v = 0; v < NV; v++)
@@ -462,7 +476,7 @@ __global__ void __launch_bounds__(nt_of(BPW), occ_hint<T>(BPW)) k_step2(StepArgs
                     for (int v = 0; v < NV; v++)
                         sm[(xlb * NV + v) * XS + xq] = xc[v];
                 }
-                if (k + 2 <= NB + 1)
+                if (k + 2 <= k1 + 1)
                     load_x(xc, k + 2);
             }
 
@@ -493,7 +507,7 @@ __global__ void __launch_bounds__(nt_of(BPW), occ_hint<T>(BPW)) k_step2(StepArgs
                     rin[2] = (Q0[q + 1] - Q0[q - 1]) * i2d[0];
                 }
             }
-            const bool dom = inI && k >= 0;
+            const bool dom = inI && k >= k0;
             // fluxes of block faces shared with another level (reflux)
             if (has) {
                 if (dof && (qx == -1 || qx == NB - 1)) {
@@ -518,7 +532,7 @@ __global__ void __launch_bounds__(nt_of(BPW), occ_hint<T>(BPW)) k_step2(StepArgs
             // ---- finalise row k-1 with the face k-1/2: y flux difference,
             //      y resistive terms, the Runge-Kutta average (WENO stage 2),
             //      psi damping (MHD-5 integrated exactly, once per step)
-            if (dom && k >= 1 && has) {
+            if (dom && k > k0 && has) {
                 T o[NV];
 #pragma unroll
                 for (int v = 0; v < NV; v++)
@@ -606,7 +620,7 @@ __global__ void __launch_bounds__(nt_of(BPW), occ_hint<T>(BPW)) k_step2(StepArgs
                 }
                 __syncthreads();
                 if (t < BPW) {
-                    const int lj = item * BPW + t;
+                    const int lj = grp * BPW + t;
                     if (lj < a.nleaves) {
                         const int cl = a.cfl_leaf[a.leaves[lj]];
                         if (cl >= 0)

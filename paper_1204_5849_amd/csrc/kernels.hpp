@@ -19,7 +19,8 @@ struct StepArgs {
     const void *Ubase;      // WENO stage 2: u^n, read at the updated cells only (may be Uout)
     const int32_t *leaves;  // leaf slots processed by this launch
     int nleaves;
-    int nitems;             // work items (groups of blocks per workgroup)
+    int nitems;             // work items (groups of blocks per workgroup, x 2^lseg)
+    int lseg;               // 2-D LF / WENO: log2 of the row segments per group, at most 4
     const BlockRec *blk;
     const map_dt *dt;
     const double *lvl_dx;

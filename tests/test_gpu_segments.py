@@ -1,0 +1,73 @@
+"""Row segments of the 2-D update: a small tree's march is split over several
+workgroups, a large one's is not.  The same small tree alone and as the first
+of many simulations (more and more blocks in one context, so 16, 8, 4, 2 and 1
+segments) must give the same state and counters bit for bit, and the oracle's
+state to round-off."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+import oracle as orc  # noqa: E402
+from paper_1204_5849_amd import native as N  # noqa: E402
+from paper_1204_5849_amd import workloads as W  # noqa: E402
+from paper_1204_5849_amd.sim import Simulation  # noqa: E402
+
+
+def _ic(wl, sim, lv, x, y, z, g):
+    tp = 2 * np.pi
+    # low pressure and cell-to-cell noise, so that the positivity fall-backs
+    # fire (the same noise in every simulation)
+    n = [W.counter_uniform(7, 0, lv, g, i) for i in range(4)]
+    zero = 0.0 * x
+    return [0.3 + 0.25 * n[0], np.sin(tp * y) + n[1], 0.7 * np.cos(tp * x) + n[2], 0.2 + zero,
+            0.3 + 0.2 * np.sin(tp * y), 0.2 + zero, 0.1 * np.cos(tp * x), 0.004 + 0.003 * n[3], zero]
+
+
+def _tree(copies, scheme, eta, riemann, precision):
+    sd = W.SimDesc(lo=(0, 0, 0), hi=(1, 1, 1), nbase=(2, 2, 1),
+                   bc=(("periodic",) * 2, ("outflow",) * 2, ("periodic",) * 2))
+    keys = []
+    for s in range(copies):
+        base = W.base_keys(s, sd.nbase, 2)
+        keys += [base, W.children_of(base[1:2], 2)]  # 7 leaves, coarse-fine faces in x and y
+    return W.Workload(name="segments", ndim=2, sims=[sd] * copies, keys=np.concatenate(keys), ic=_ic,
+                      scheme=scheme, eta=eta, riemann=riemann, precision=precision)
+
+
+def _run(w):
+    s = Simulation(w, device="cuda:0")
+    s.load_initial()
+    s.flags()
+    s.advance(3)
+    s.sync()
+    inner = s.state_by_key()[:, :, :, 2:-2, 2:-2]
+    return inner, s.flags()[1], s.dt.cpu().numpy()
+
+
+@pytest.mark.parametrize("scheme,eta,riemann,precision", [("lf", 1e-3, "rusanov", "fp64"),
+                                                          ("weno", 0.0, "hllc", "fp64"),
+                                                          ("lf", 0.0, "hllc", "fp32"),
+                                                          ("weno", 1e-3, "rusanov", "fp32")])
+def test_segments_do_not_change_the_update(scheme, eta, riemann, precision):
+    N.lib()
+    one, cnt, dt = _run(_tree(1, scheme, eta, riemann, precision))
+    assert np.isfinite(one).all()
+    if precision == "fp64":
+        w = _tree(1, scheme, eta, riemann, precision)
+        A = orc.load_workload(w)
+        A.run(3)
+        o = A.state[:, :, :, 2:-2, 2:-2]
+        for k in range(8):
+            assert np.abs(one[:, k] - o[:, k]).max() <= 1e-11 * np.abs(o[:, k]).max()
+    # 14 blocks per workgroup: 40 copies are 20 groups, 80 are 40, 150 are 75, 300 are 150
+    for copies in (40, 80, 150, 300):
+        many, cm, dm = _run(_tree(copies, scheme, eta, riemann, precision))
+        n = len(one)
+        for s in (0, copies // 2, copies - 1):
+            assert np.array_equal(many[s * n:(s + 1) * n], one), f"{copies} copies, simulation {s}"
+        assert np.array_equal(dm, np.repeat(dt, copies, axis=0))
+        assert cm == [copies * c for c in cnt]
+    assert cnt[1 if scheme == "weno" else 0] > 0
