@@ -83,6 +83,21 @@ map_status scratch_of_current_device(double **out)
 
 bool fp64(const map_ctx *c) { return c->p.precision == MAP_FP64; }
 
+// how the copies of n frames are cut into work items: blocks per item (2-D,
+// 144 ghost cells each), items per block (3-D, 3904 cells).  A thread's cells
+// are a chain of descriptor, source and store, so short lists take as many
+// items as give every thread one cell: 18.6 -> 5.5 us
+// for the 88 frames of a 2-D tree, 37 -> 22 us for the blast's 128, 29.6 ->
+// 10.4 us for 32 FP64 ones
+void fill_split(const map_ctx *c, int n, int &bpw, int &parts)
+{
+    bpw = c->nd == 3 || n < 16 * c->ncu ? 1 : 16;
+    parts = 1;
+    if (c->nd == 3)
+        while (parts < 16 && (long long)2 * parts * n <= 8 * c->ncu)
+            parts *= 2;
+}
+
 // Ghost fill: same-level copies, then prolongation level by level (coarse to
 // fine).  `all`: the copies fill every slot's ghost frame; otherwise only
 // the frames the prolongation reads (the step reads same-level neighbour
@@ -102,18 +117,20 @@ map_status run_fill(map_ctx *c, void *U, hipStream_t s, bool all, int eonly_sub 
     a.copy_list = all ? nullptr : dptr<int32_t>(c, c->ws.frame_list);
     a.copy_sel = all ? nullptr : dptr<FrameSel>(c, c->ws.frame_sel);
     const int ncopy = all ? c->nslots : (int)c->frame_list.size();
-    const int bpw = fill_blocks_per_group(c->nd);
+    fill_split(c, ncopy, a.bpw, a.parts);
     if (c->launch_mode == MAP_LAUNCH_PER_BLOCK) {
         for (int i = 0; i < ncopy; i++) {
             a.slot_base = i;
             a.slot_end = i + 1;
+            a.bpw = 1;
+            a.parts = 1;
             a.nitems = 1;
             HIPCHK(launch_fill_copy(c->nd, fp64(c), a, 1, s));
         }
     } else if (ncopy > 0) {
         a.slot_base = 0;
         a.slot_end = ncopy;
-        a.nitems = (ncopy + bpw - 1) / bpw;
+        a.nitems = (ncopy + a.bpw - 1) / a.bpw * a.parts;
         HIPCHK(launch_fill_copy(c->nd, fp64(c), a, c->grid_fill, s));
     }
     for (int l = 2; l <= c->lmax; l++) {
@@ -122,7 +139,8 @@ map_status run_fill(map_ctx *c, void *U, hipStream_t s, bool all, int eonly_sub 
             continue;
         a.list = dptr<int32_t>(c, c->ws.prolong_list) + lo;
         a.list_mask = dptr<uint32_t>(c, c->ws.prolong_mask) + lo;
-        a.nitems = hi - lo;
+        a.parts = eonly_sub < 0 && hi - lo < 4 * c->ncu ? 3 : 1;
+        a.nitems = (hi - lo) * a.parts;
         HIPCHK(launch_prolong_ghosts(c->nd, fp64(c), a, s));
     }
     return MAP_OK;
@@ -191,6 +209,7 @@ map_status run_cfl(map_ctx *c, const void *U, map_dt *dt_out, hipStream_t s,
     a.U = U;
     a.cnt = dptr<unsigned long long>(c, c->ws.counters);
     a.gamma = c->p.gamma;
+    a.wide_below = 4 * c->ncu;
     const bool cond = c->p.cond_mode != MAP_COND_OFF;
     a.kappa0 = c->p.kappa0;
     a.khalf = (int)(2.0 * c->p.kappa_exp + 0.5);
@@ -238,6 +257,7 @@ map_status run_cfl_rest(map_ctx *c, const void *U, hipStream_t s, map_dt *dt_int
         a.U = U;
         a.cnt = dptr<unsigned long long>(c, c->ws.counters);
         a.gamma = c->p.gamma;
+        a.wide_below = 4 * c->ncu;
         a.leaves = dptr<int32_t>(c, fused ? c->ws.orphans_rest : c->ws.orphans);
         a.nleaves = (int)n;
         a.part = dptr<double>(c, c->ws.cfl_part);
@@ -357,6 +377,7 @@ map_status run_reflux(map_ctx *c, void *U, const map_dt *dt, hipStream_t s, int 
     a.lvl_dx = dptr<double>(c, c->ws.lvl_dx);
     a.fbuf = c->wsp + c->ws.fbuf;
     a.nitems = (int)c->reflux_slots.size();
+    a.vsplit = !a.eonly && c->nd == 3 && a.nitems < c->ncu;
     HIPCHK(launch_reflux(c->nd, fp64(c), a, s));
     return MAP_OK;
 }
@@ -1034,10 +1055,10 @@ map_status map_autotune(map_ctx *c, void *U, int *chosen, void *stream)
     c->step_shape = best_shape;
     c->grid_step = best_step;
     // the parent-frame copies of the cycle's fill
-    const int fbpw = fill_blocks_per_group(c->nd);
-    int best_fill = 0;
+    int fbpw, fparts, best_fill = 0;
+    fill_split(c, (int)c->frame_list.size(), fbpw, fparts);
     best_t = 1e30f;
-    for (int g : grids(((int)c->frame_list.size() + fbpw - 1) / fbpw)) {
+    for (int g : grids(((int)c->frame_list.size() + fbpw - 1) / fbpw * fparts)) {
         c->grid_fill = g;
         float t = time_it([&] { return run_fill(c, U, s, false); });
         if (faster(t, best_t)) {

@@ -23,12 +23,11 @@ template <int NDIM>
 struct FG;
 template <>
 struct FG<2> {
-    static constexpr int P = PD * PD, NGC = PD * PD - NB * NB, BPW = 16, NI = NB * NB;
+    static constexpr int P = PD * PD, NGC = PD * PD - NB * NB, NI = NB * NB;
 };
 template <>
 struct FG<3> {
-    static constexpr int P = PD * PD * PD, NGC = PD * PD * PD - NB * NB * NB, BPW = 1,
-                         NI = NB * NB * NB;
+    static constexpr int P = PD * PD * PD, NGC = PD * PD * PD - NB * NB * NB, NI = NB * NB * NB;
 };
 constexpr int NTA = 256;
 
@@ -101,7 +100,7 @@ __device__ __forceinline__ bool sub_inactive(const map_dt *dt, int sim, int sub)
 template <int NDIM, typename T, bool EO>
 __global__ void __launch_bounds__(NTA) k_fill_copy(FillArgs a)
 {
-    constexpr int P = FG<NDIM>::P, NGC = FG<NDIM>::NGC, BPW = FG<NDIM>::BPW;
+    constexpr int P = FG<NDIM>::P, NGC = FG<NDIM>::NGC;
     constexpr int K0 = VarRange<EO>::K0, K1 = VarRange<EO>::K1;
     T *U = (T *)a.U;
     if (EO && sub_idle(a.dt, a.nsims, a.sub))
@@ -109,13 +108,18 @@ __global__ void __launch_bounds__(NTA) k_fill_copy(FillArgs a)
     int first, stride, end;
     xcd_range(a.nitems, first, stride, end);
     for (int item = first; item < end; item += stride) {
+        // an item is one of `parts` shares of a block's frame (3-D), or
+        // `bpw` whole blocks (2-D)
+        const int grp = NDIM == 3 ? item / a.parts : item;
+        const int bpw = NDIM == 3 ? 1 : a.bpw;
         // one block per item (3-D): its selection is loaded once
         FrameSel f1{~0u, {-NG, -NG, -NG}, {NB + NG - 1, NB + NG - 1, NB + NG - 1}, 0};
-        if (BPW == 1 && a.copy_sel && a.slot_base + item < a.slot_end)
-            f1 = a.copy_sel[a.slot_base + item];
-        for (int g = threadIdx.x; g < BPW * NGC; g += NTA) {
-            const int lb = g / NGC, gi = g - lb * NGC;
-            const int i = a.slot_base + item * BPW + lb;
+        if (NDIM == 3 && a.copy_sel && a.slot_base + grp < a.slot_end)
+            f1 = a.copy_sel[a.slot_base + grp];
+        const int g0 = NDIM == 3 ? (item - grp * a.parts) * NTA : 0, gs = NDIM == 3 ? a.parts * NTA : NTA;
+        for (int g = g0 + threadIdx.x; g < bpw * NGC; g += gs) {
+            const int lb = NDIM == 3 ? 0 : g / NGC, gi = g - lb * NGC;
+            const int i = a.slot_base + grp * bpw + lb;
             if (i >= a.slot_end)
                 break;
             const int slot = a.copy_list ? a.copy_list[i] : i;
@@ -124,8 +128,8 @@ __global__ void __launch_bounds__(NTA) k_fill_copy(FillArgs a)
             int x, y, z;
             ghost_xyz<NDIM>(gi, x, y, z);
             const int di = dir_index<NDIM>(x, y, z);
-            if (BPW == 1 || a.copy_sel) {
-                const FrameSel &f = BPW == 1 ? f1 : a.copy_sel[i];
+            if (NDIM == 3 || a.copy_sel) {
+                const FrameSel &f = NDIM == 3 ? f1 : a.copy_sel[i];
                 if (!((f.dirs >> di) & 1u) || x < f.lo[0] || x > f.hi[0] || y < f.lo[1] ||
                     y > f.hi[1] || (NDIM == 3 && (z < f.lo[2] || z > f.hi[2])))
                     continue;
@@ -225,6 +229,10 @@ __device__ __forceinline__ void group_xyz(int g, int &X, int &Y, int &Z)
     }
 }
 
+// A short list takes three workgroups per block, three variables each
+// (a.parts): the group loop is one long chain of 63 loads and 36 stores,
+// 29.7 -> 26.0 us on the blast's 632 blocks, 20.6 -> 13.4 on 176 FP64 ones,
+// 17.9 -> 13.5 on 512
 template <int NDIM, typename T, bool EO>
 __global__ void __launch_bounds__(NTA) k_prolong_ghosts(FillArgs a)
 {
@@ -237,7 +245,9 @@ __global__ void __launch_bounds__(NTA) k_prolong_ghosts(FillArgs a)
         return;
     int first, stride, end;
     xcd_range(a.nitems, first, stride, end);  // siblings share the parent tile in L2
-    for (int item = first; item < end; item += stride) {
+    for (int it = first; it < end; it += stride) {
+        const int item = EO ? it : it / a.parts;
+        const int kw = EO ? K1 - K0 : NV / a.parts, k0 = EO ? K0 : (it - item * a.parts) * kw;
         const int slot = a.list[item];
         if (EO && sub_inactive(a.dt, a.blk[slot].sim, a.sub))
             continue;
@@ -258,8 +268,8 @@ __global__ void __launch_bounds__(NTA) k_prolong_ghosts(FillArgs a)
                                     NDIM == 3 ? ((cpos >> 2) & 1) * H + Z : 0);
             const int st[3] = {1, PD, PD * PD};
             const int f0 = lin<NDIM>(x, y, z);
-#pragma unroll
-            for (int k = K0; k < K1; k++) {
+#pragma unroll 3
+            for (int k = k0; k < k0 + kw; k++) {
                 const T *q = pu + (size_t)k * P;
                 const T val = q[c];
                 T sw[3];  // quarter slope along each dimension
@@ -332,17 +342,24 @@ __global__ void __launch_bounds__(NTA) k_prolong_blocks(FillArgs a)
 // thread keeps its maxima per half, and the workgroup combines them per
 // child with LDS atomics on the bit patterns (the speeds are finite and
 // non-negative, so those order like the values).
-template <int NDIM, typename T, bool EO, bool CFL = false>
-__global__ void __launch_bounds__(NTA) k_restrict(RestrictArgs a)
+// PC: per child, one parent cell per thread (512 threads in 3-D, 64 in 2-D):
+// 30.8 -> 26.1 us for 256 FP64 children, 26.4 -> 19.5 for 256 FP32 ones
+constexpr int nt_restrict(int ndim, bool pc)
 {
+    return pc ? (ndim == 3 ? NB * NB * NB / 8 : NB * NB / 4) : NTA;
+}
+template <int NDIM, typename T, bool EO, bool CFL, bool PC>
+__global__ void __launch_bounds__(nt_restrict(NDIM, PC)) k_restrict(RestrictArgs a)
+{
+    constexpr int NT = nt_restrict(NDIM, PC);
     using V = typename Pair<T>::V;
     constexpr int P = FG<NDIM>::P, NI = FG<NDIM>::NI;
     constexpr int K0 = VarRange<EO>::K0, K1 = VarRange<EO>::K1;
     constexpr int NCH = NDIM == 3 ? 8 : 4, NC = NDIM == 3 ? 8 : 4;
-    constexpr int H = NB / 2, NO = NDIM == 3 ? H * H * H : H * H;  // parent cells per child
+    constexpr int H = NB / 2;
     static_assert(!CFL || (!EO && NTA == NB * NB), "CFL: all variables, one column per thread");
     __shared__ unsigned long long smax[CFL ? NCH : 1];
-    __shared__ double red[CFL ? NTA / 64 : 1];
+    __shared__ double red[CFL ? NT / 64 : 1];
     T *U = (T *)a.U;
     if (EO && sub_idle(a.dt, a.nsims, a.sub))
         return;
@@ -409,7 +426,7 @@ __global__ void __launch_bounds__(NTA) k_restrict(RestrictArgs a)
         if (nonfin)
             atomicAdd(&a.cnt[3], (unsigned long long)nonfin);
     };
-    if (a.per_child) {
+    if constexpr (PC) {
         // one workgroup per child: the parent's octant (quadrant) it covers
         for (int item = blockIdx.x; item < a.nitems; item += gridDim.x) {
             const int slot = a.list[item / NCH];
@@ -424,8 +441,9 @@ __global__ void __launch_bounds__(NTA) k_restrict(RestrictArgs a)
             const bool leafc = CFL && a.leaf_of[child] >= 0;
             double m = 0.0;
             unsigned bad = 0, nonfin = 0;
-            for (int i = threadIdx.x; i < NO; i += NTA) {
-                const int x = i % H, y = (i / H) % H, z = NDIM == 3 ? i / (H * H) : 0;
+            {
+                const int i = threadIdx.x, x = i % H, y = (i / H) % H,
+                          z = NDIM == 3 ? i / (H * H) : 0;
                 T cv[CFL ? NV : 1][CFL ? NC : 1];
                 restrict_cell(ub, cu, lin<NDIM>(2 * x, 2 * y, 2 * z), lin<NDIM>(ox + x, oy + y, oz + z),
                               cv);
@@ -445,58 +463,62 @@ __global__ void __launch_bounds__(NTA) k_restrict(RestrictArgs a)
                 __syncthreads();
                 if (threadIdx.x == 0 && leafc) {
                     double r = red[0];
-                    for (int w = 1; w < NTA / 64; w++)
+                    for (int w = 1; w < NT / 64; w++)
                         r = red[w] > r ? red[w] : r;
                     a.part[a.leaf_of[child]] = r;
                 }
                 __syncthreads();
             }
         }
-        return;
-    }
-    for (int item = blockIdx.x; item < a.nitems; item += gridDim.x) {
-        const int slot = a.list[item];
-        if (EO && sub_inactive(a.dt, a.blk[slot].sim, a.sub))
-            continue;
-        T *ub = U + (size_t)slot * NV * P;
-        double m[2] = {0.0, 0.0};
-        unsigned bad = 0, nonfin = 0;
-        if constexpr (CFL) {
-            if (threadIdx.x < NCH)
-                smax[threadIdx.x] = 0ull;
-            __syncthreads();
-        }
-        for (int i = threadIdx.x; i < NI; i += NTA) {
-            const int X = i % NB, Y = (i / NB) % NB, Z = NDIM == 3 ? i / (NB * NB) : 0;
-            const int fx = 2 * X, fy = 2 * Y, fz = 2 * Z;
-            const int cbit = (fx / NB) | ((fy / NB) << 1) | (NDIM == 3 ? (fz / NB) << 2 : 0);
-            const int child = a.children[(size_t)slot * 8 + cbit];
-            const T *cu = U + (size_t)child * NV * P;
-            const int lx = fx % NB, ly = fy % NB, lz = NDIM == 3 ? fz % NB : 0;
-            T cv[CFL ? NV : 1][CFL ? NC : 1];
-            restrict_cell(ub, cu, lin<NDIM>(lx, ly, lz), lin<NDIM>(X, Y, Z), cv);
-            if (CFL && a.leaf_of[child] >= 0)
-                cell_speeds(cv, m[NDIM == 3 ? fz / NB : 0], bad, nonfin);
-        }
-        if constexpr (CFL) {
-            // this thread's children: the one of its column below the middle
-            // in z, and (3-D) the one above it
-            const int cb = (threadIdx.x % NB >= NB / 2) | ((threadIdx.x / NB >= NB / 2) << 1);
-            atomicMax(&smax[cb], (unsigned long long)__double_as_longlong(m[0]));
-            if constexpr (NDIM == 3)
-                atomicMax(&smax[cb | 4], (unsigned long long)__double_as_longlong(m[1]));
-            count(bad, nonfin);
-            __syncthreads();
-            if (threadIdx.x < NCH) {
-                const int li = a.leaf_of[a.children[(size_t)slot * 8 + threadIdx.x]];
-                if (li >= 0)
-                    a.part[li] = __longlong_as_double((long long)smax[threadIdx.x]);
+    } else {
+        for (int item = blockIdx.x; item < a.nitems; item += gridDim.x) {
+            const int slot = a.list[item];
+            if (EO && sub_inactive(a.dt, a.blk[slot].sim, a.sub))
+                continue;
+            T *ub = U + (size_t)slot * NV * P;
+            double m[2] = {0.0, 0.0};
+            unsigned bad = 0, nonfin = 0;
+            if constexpr (CFL) {
+                if (threadIdx.x < NCH)
+                    smax[threadIdx.x] = 0ull;
+                __syncthreads();
+            }
+            for (int i = threadIdx.x; i < NI; i += NTA) {
+                const int X = i % NB, Y = (i / NB) % NB, Z = NDIM == 3 ? i / (NB * NB) : 0;
+                const int fx = 2 * X, fy = 2 * Y, fz = 2 * Z;
+                const int cbit = (fx / NB) | ((fy / NB) << 1) | (NDIM == 3 ? (fz / NB) << 2 : 0);
+                const int child = a.children[(size_t)slot * 8 + cbit];
+                const T *cu = U + (size_t)child * NV * P;
+                const int lx = fx % NB, ly = fy % NB, lz = NDIM == 3 ? fz % NB : 0;
+                T cv[CFL ? NV : 1][CFL ? NC : 1];
+                restrict_cell(ub, cu, lin<NDIM>(lx, ly, lz), lin<NDIM>(X, Y, Z), cv);
+                if (CFL && a.leaf_of[child] >= 0)
+                    cell_speeds(cv, m[NDIM == 3 ? fz / NB : 0], bad, nonfin);
+            }
+            if constexpr (CFL) {
+                // this thread's children: the one of its column below the middle
+                // in z, and (3-D) the one above it
+                const int cb = (threadIdx.x % NB >= NB / 2) | ((threadIdx.x / NB >= NB / 2) << 1);
+                atomicMax(&smax[cb], (unsigned long long)__double_as_longlong(m[0]));
+                if constexpr (NDIM == 3)
+                    atomicMax(&smax[cb | 4], (unsigned long long)__double_as_longlong(m[1]));
+                count(bad, nonfin);
+                __syncthreads();
+                if (threadIdx.x < NCH) {
+                    const int li = a.leaf_of[a.children[(size_t)slot * 8 + threadIdx.x]];
+                    if (li >= 0)
+                        a.part[li] = __longlong_as_double((long long)smax[threadIdx.x]);
+                }
             }
         }
     }
 }
 
-// ---- reflux: one workgroup per coarse leaf, its faces in a fixed order
+// ---- reflux: the faces of a coarse leaf in a fixed order (two faces share
+// their edge cells).  Variables do not meet, so a list shorter than the CUs
+// takes a workgroup per variable of a leaf (a.vsplit), which cuts a face from
+// nine passes of 256 cells to one: 31.6 -> 24.6 us on the blast's 120 leaves,
+// 18.9 -> 17.7 on 24, but 22.2 -> 24.8 on 672, where the chip was full
 template <int NDIM, typename T, bool EO>
 __global__ void __launch_bounds__(NTA) k_reflux(RefluxArgs a)
 {
@@ -507,7 +529,10 @@ __global__ void __launch_bounds__(NTA) k_reflux(RefluxArgs a)
     const T *fb = (const T *)a.fbuf;
     if (EO && sub_idle(a.dt, a.nsims, a.sub))
         return;
-    for (int item = blockIdx.x; item < a.nitems; item += gridDim.x) {
+    const int nsh = a.vsplit ? K1 - K0 : 1;  // workgroups per leaf
+    for (int it = blockIdx.x; it < a.nitems * nsh; it += gridDim.x) {
+        const int item = it / nsh;
+        const int v0 = a.vsplit ? K0 + it - item * nsh : K0, v1 = a.vsplit ? v0 + 1 : K1;
         const int slot = a.slots[item];
         const BlockRec br = a.blk[slot];
         if (EO && sub_inactive(a.dt, br.sim, a.sub))
@@ -519,8 +544,8 @@ __global__ void __launch_bounds__(NTA) k_reflux(RefluxArgs a)
             const RefluxRec r = a.recs[e];
             const T dtdx = (T)(dtv / dxp[r.dim]);
             const int t1 = r.dim == 0 ? 1 : 0, t2 = r.dim == 2 ? 1 : 2;
-            for (int idx = threadIdx.x; idx < FC * (K1 - K0); idx += NTA) {
-                const int k = K0 + idx / FC, tt = idx - (k - K0) * FC;
+            for (int idx = threadIdx.x; idx < FC * (v1 - v0); idx += NTA) {
+                const int k = v0 + idx / FC, tt = idx - (k - v0) * FC;
                 const int ta = tt % NB, tb = NDIM == 3 ? tt / NB : 0;
                 T f[4];
                 const int nf = NDIM == 3 ? 4 : 2;
@@ -555,18 +580,21 @@ __global__ void __launch_bounds__(NTA) k_reflux(RefluxArgs a)
 }
 
 // ---- CFL: per leaf, max over interior cells of max_d |v_d| + c_f,d (FP64)
-template <int NDIM, typename T>
-__global__ void __launch_bounds__(NTA) k_cfl(CflArgs a)
+// A thread's cells are a chain of FP64 roots; a list too short to fill the
+// chip takes four times the threads per leaf (NT = 1024 in 3-D): 31 -> 21 us on
+// the blast's 376 base leaves, 24.7 -> 11.2 on 32 FP64 leaves
+template <int NDIM, typename T, int NT>
+__global__ void __launch_bounds__(NT) k_cfl(CflArgs a)
 {
     constexpr int P = FG<NDIM>::P, NI = FG<NDIM>::NI;
-    __shared__ double red[NTA / 64];
+    __shared__ double red[NT / 64];
     const T *U = (const T *)a.U;
     for (int item = blockIdx.x; item < a.nleaves; item += gridDim.x) {
         const int slot = a.leaves[item];
         const T *ub = U + (size_t)slot * NV * P;
         double m = 0.0, cm = 0.0;
         unsigned bad = 0, nonfin = 0;
-        for (int i = threadIdx.x; i < NI; i += NTA) {
+        for (int i = threadIdx.x; i < NI; i += NT) {
             const int x = i % NB, y = (i / NB) % NB, z = NDIM == 3 ? i / (NB * NB) : 0;
             const int c = lin<NDIM>(x, y, z);
             double u[NV];
@@ -596,7 +624,7 @@ __global__ void __launch_bounds__(NTA) k_cfl(CflArgs a)
             atomicAdd(&a.cnt[2], (unsigned long long)bad);
         if (nonfin)
             atomicAdd(&a.cnt[3], (unsigned long long)nonfin);
-        // wave64 shuffle max, then across the 4 waves through LDS
+        // wave64 shuffle max, then across the waves through LDS
         auto block_max = [&](double v) {
 #pragma unroll
             for (int off = 32; off > 0; off >>= 1) {
@@ -608,7 +636,7 @@ __global__ void __launch_bounds__(NTA) k_cfl(CflArgs a)
                 red[w] = v;
             __syncthreads();
             double r = red[0];
-            for (int i = 1; i < NTA / 64; i++)
+            for (int i = 1; i < NT / 64; i++)
                 r = red[i] > r ? red[i] : r;
             __syncthreads();
             return r;
@@ -809,21 +837,6 @@ __global__ void k_clear_u64(unsigned long long *p, int n)
     } while (0)
 
 // as DISPATCH, for kernels with an energy-only variant chosen by a.eonly
-#define DISPATCH_CFL(ndim, fp64, ...)                                               \
-    do {                                                                            \
-        if (ndim == 2) {                                                            \
-            if (fp64)                                                               \
-                hipLaunchKernelGGL((k_restrict<2, double, false, true>), __VA_ARGS__); \
-            else                                                                    \
-                hipLaunchKernelGGL((k_restrict<2, float, false, true>), __VA_ARGS__); \
-        } else {                                                                    \
-            if (fp64)                                                               \
-                hipLaunchKernelGGL((k_restrict<3, double, false, true>), __VA_ARGS__); \
-            else                                                                    \
-                hipLaunchKernelGGL((k_restrict<3, float, false, true>), __VA_ARGS__); \
-        }                                                                           \
-    } while (0)
-
 #define DISPATCH_EO(ndim, fp64, eo, KER, ...)                                       \
     do {                                                                            \
         if (eo) {                                                                   \
@@ -853,7 +866,6 @@ __global__ void k_clear_u64(unsigned long long *p, int n)
         }                                                                           \
     } while (0)
 
-int fill_blocks_per_group(int ndim) { return ndim == 3 ? FG<3>::BPW : FG<2>::BPW; }
 
 hipError_t launch_fill_copy(int ndim, bool fp64, const FillArgs &a, int grid, hipStream_t s)
 {
@@ -883,18 +895,38 @@ hipError_t launch_prolong_blocks(int ndim, bool fp64, const FillArgs &a, hipStre
     return hipGetLastError();
 }
 
+template <int NDIM, typename T, bool EO, bool CFL>
+static void launch_restrict_pc(const RestrictArgs &a, int g, hipStream_t s)
+{
+    if (a.per_child)
+        hipLaunchKernelGGL((k_restrict<NDIM, T, EO, CFL, true>), dim3(g),
+                           dim3(nt_restrict(NDIM, true)), 0, s, a);
+    else
+        hipLaunchKernelGGL((k_restrict<NDIM, T, EO, CFL, false>), dim3(g), dim3(NTA), 0, s, a);
+}
+
+template <int NDIM, typename T>
+static void launch_restrict_t(const RestrictArgs &a, hipStream_t s)
+{
+    const int g = a.eonly && a.nitems > SUB_GRID ? SUB_GRID : a.nitems;
+    if (a.cfl)
+        launch_restrict_pc<NDIM, T, false, true>(a, g, s);
+    else if (a.eonly)
+        launch_restrict_pc<NDIM, T, true, false>(a, g, s);
+    else
+        launch_restrict_pc<NDIM, T, false, false>(a, g, s);
+}
+
 hipError_t launch_restrict(int ndim, bool fp64, const RestrictArgs &a, hipStream_t s)
 {
     if (a.nitems <= 0)
         return hipSuccess;
-    if (a.cfl) {
-        if (a.eonly)
-            return hipErrorInvalidValue;
-        DISPATCH_CFL(ndim, fp64, dim3(a.nitems), dim3(NTA), 0, s, a);
-    } else {
-        const int g = a.eonly && a.nitems > SUB_GRID ? SUB_GRID : a.nitems;
-        DISPATCH_EO(ndim, fp64, a.eonly, k_restrict, dim3(g), dim3(NTA), 0, s, a);
-    }
+    if (a.cfl && a.eonly)
+        return hipErrorInvalidValue;
+    if (ndim == 2)
+        fp64 ? launch_restrict_t<2, double>(a, s) : launch_restrict_t<2, float>(a, s);
+    else
+        fp64 ? launch_restrict_t<3, double>(a, s) : launch_restrict_t<3, float>(a, s);
     return hipGetLastError();
 }
 
@@ -902,7 +934,8 @@ hipError_t launch_reflux(int ndim, bool fp64, const RefluxArgs &a, hipStream_t s
 {
     if (a.nitems <= 0)
         return hipSuccess;
-    const int g = a.eonly && a.nitems > SUB_GRID ? SUB_GRID : a.nitems;
+    const int n = a.vsplit && !a.eonly ? a.nitems * NV : a.nitems;
+    const int g = a.eonly && n > SUB_GRID ? SUB_GRID : n;
     DISPATCH_EO(ndim, fp64, a.eonly, k_reflux, dim3(g), dim3(NTA), 0, s, a);
     return hipGetLastError();
 }
@@ -911,7 +944,22 @@ hipError_t launch_cfl(int ndim, bool fp64, const CflArgs &a, hipStream_t s)
 {
     if (a.nleaves <= 0)
         return hipSuccess;
-    DISPATCH(ndim, fp64, k_cfl, dim3(a.nleaves), dim3(NTA), 0, s, a);
+    if (ndim == 2) {
+        if (fp64)
+            hipLaunchKernelGGL((k_cfl<2, double, NTA>), dim3(a.nleaves), dim3(NTA), 0, s, a);
+        else
+            hipLaunchKernelGGL((k_cfl<2, float, NTA>), dim3(a.nleaves), dim3(NTA), 0, s, a);
+    } else if (a.nleaves < a.wide_below) {
+        if (fp64)
+            hipLaunchKernelGGL((k_cfl<3, double, 1024>), dim3(a.nleaves), dim3(1024), 0, s, a);
+        else
+            hipLaunchKernelGGL((k_cfl<3, float, 1024>), dim3(a.nleaves), dim3(1024), 0, s, a);
+    } else {
+        if (fp64)
+            hipLaunchKernelGGL((k_cfl<3, double, NTA>), dim3(a.nleaves), dim3(NTA), 0, s, a);
+        else
+            hipLaunchKernelGGL((k_cfl<3, float, NTA>), dim3(a.nleaves), dim3(NTA), 0, s, a);
+    }
     return hipGetLastError();
 }
 

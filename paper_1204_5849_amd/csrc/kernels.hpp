@@ -54,6 +54,8 @@ struct FillArgs {
     const int32_t *copy_list;  // copies: slots (null: slot = index)
     const FrameSel *copy_sel;  // copies: ghost cells to fill per list entry (null: all)
     int slot_base, slot_end, nitems;  // copies: index range [slot_base, slot_end)
+    int bpw, parts;            // copies: blocks per item (2-D), items per block (3-D);
+                               // prolongation: items per block, 1 or 3 (NV / parts variables each)
     const map_dt *dt;
     int eonly, sub, nsims;
 };
@@ -86,7 +88,7 @@ struct RefluxArgs {
     const map_dt *dt;
     const double *lvl_dx;
     const void *fbuf;
-    int nitems;
+    int nitems, vsplit;     // leaves; whether each variable of a leaf takes a workgroup
     int eonly, sub, nsims;  // conduction sub-step: energy only, dt_sub
 };
 
@@ -100,6 +102,7 @@ struct CflArgs {
     unsigned long long *cnt;
     double gamma, kappa0;
     int khalf;      // 2 x kappa exponent
+    int wide_below; // 3-D lists shorter than this take 1024 threads per leaf
 };
 
 struct DtArgs {
@@ -183,7 +186,6 @@ hipError_t launch_step_mmc3(bool fp64, bool resist, const StepArgs &a, int grid,
 // blocks per workgroup of the batched update for a workgroup shape (StepArgs::shape)
 int step_blocks_per_group(int ndim, int scheme, int shape);
 hipError_t launch_fill_copy(int ndim, bool fp64, const FillArgs &a, int grid, hipStream_t s);
-int fill_blocks_per_group(int ndim);
 hipError_t launch_prolong_ghosts(int ndim, bool fp64, const FillArgs &a, hipStream_t s);
 hipError_t launch_prolong_blocks(int ndim, bool fp64, const FillArgs &a, hipStream_t s);
 hipError_t launch_restrict(int ndim, bool fp64, const RestrictArgs &a, hipStream_t s);

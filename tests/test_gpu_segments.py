@@ -2,7 +2,8 @@
 workgroups, a large one's is not.  The same small tree alone and as the first
 of many simulations (more and more blocks in one context, so 16, 8, 4, 2 and 1
 segments) must give the same state and counters bit for bit, and the oracle's
-state to round-off."""
+state to round-off.  The 3-D data-motion passes likewise cut short lists into
+more workgroups than long ones."""
 import numpy as np
 import pytest
 
@@ -71,3 +72,40 @@ def test_segments_do_not_change_the_update(scheme, eta, riemann, precision):
         assert np.array_equal(dm, np.repeat(dt, copies, axis=0))
         assert cm == [copies * c for c in cnt]
     assert cnt[1 if scheme == "weno" else 0] > 0
+
+
+@pytest.mark.parametrize("scheme,precision", [("lf", "fp64"), ("mmc", "fp32")])
+def test_short_and_long_lists_3d(scheme, precision):
+    """One 3-D tree (a parent, 15 leaves, 7 of them with reflux faces) alone and
+    as many copies: 1, 40 and 300 parents, 7 to 2100 reflux leaves, 8 to 2400
+    blocks with prolongated ghosts, 7 to 2100 base leaves in the CFL pass."""
+    sd = W.SimDesc(lo=(0, 0, 0), hi=(1, 1, 1), nbase=(2, 2, 2),
+                   bc=(("periodic",) * 2, ("outflow",) * 2, ("periodic",) * 2))
+
+    def tree(copies):
+        keys = []
+        for s in range(copies):
+            base = W.base_keys(s, sd.nbase, 3)
+            keys += [base, W.children_of(base[3:4], 3)]
+        return W.Workload(name="lists", ndim=3, sims=[sd] * copies, keys=np.concatenate(keys),
+                          ic=lambda wl, sim, lv, x, y, z, g: [
+                              1 + 0.3 * np.sin(2 * np.pi * (x + z)), 0.4 * np.cos(2 * np.pi * y) + 0 * x,
+                              0.3 * np.sin(2 * np.pi * x), 0.2 * np.cos(2 * np.pi * z), 0.5 + 0 * x,
+                              0.4 + 0.1 * np.sin(2 * np.pi * y), 0.3 + 0 * x, 0.6 + 0 * x, 0 * x],
+                          scheme=scheme, precision=precision, glm_mode="fastspeed")
+
+    def run(w):
+        s = Simulation(w, device="cuda:0")
+        s.load_initial()
+        s.advance(2)
+        s.fill()
+        s.sync()
+        first = np.arange(16)
+        last = len(w.keys) - 16 + first
+        return s.state_by_key(first), s.state_by_key(last), s.totals()
+
+    one, _, tot = run(tree(1))
+    for copies in (40, 300):
+        a, b, t = run(tree(copies))
+        assert np.array_equal(a, one) and np.array_equal(b, one), copies
+        assert np.array_equal(t, np.repeat(tot, copies, axis=0))
