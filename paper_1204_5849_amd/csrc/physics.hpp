@@ -21,6 +21,15 @@ struct Num<double> {
     static __device__ __forceinline__ double rcp(double x) { return rcp64(x); }
     static __device__ __forceinline__ double sqrt_(double x) { return sqrt64(x); }
     static __device__ __forceinline__ double div(double a, double b) { return div64(a, b); }
+    static __device__ __forceinline__ double max_(double a, double b) { return __builtin_fmax(a, b); }
+    static __device__ __forceinline__ double min_(double a, double b) { return __builtin_fmin(a, b); }
+    // b where the mask m is 0, a where it is all ones
+    static __device__ __forceinline__ double pick(unsigned m, double a, double b)
+    {
+        const unsigned lo = (m & (unsigned)__double2loint(a)) | (~m & (unsigned)__double2loint(b));
+        const unsigned hi = (m & (unsigned)__double2hiint(a)) | (~m & (unsigned)__double2hiint(b));
+        return __hiloint2double((int)hi, (int)lo);
+    }
 };
 
 template <>
@@ -28,6 +37,11 @@ struct Num<float> {
     static __device__ __forceinline__ float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
     static __device__ __forceinline__ float sqrt_(float x) { return __builtin_amdgcn_sqrtf(x); }
     static __device__ __forceinline__ float div(float a, float b) { return a * __builtin_amdgcn_rcpf(b); }
+    static __device__ __forceinline__ float max_(float a, float b) { return __builtin_fmaxf(a, b); }
+    static __device__ __forceinline__ float pick(unsigned m, float a, float b)
+    {
+        return __uint_as_float((m & __float_as_uint(a)) | (~m & __float_as_uint(b)));
+    }
 };
 
 // conduction coefficient kappa = kappa0 T^(khalf/2) (Sec. 3.4): whole
@@ -42,22 +56,14 @@ __device__ __forceinline__ double kappa_of(double kappa0, int khalf, double T)
     return kappa0 * q;
 }
 
-template <typename T>
-__device__ __forceinline__ T sgn_of(T a)
-{
-    return a > T(0) ? T(1) : (a < T(0) ? T(-1) : T(0));
-}
-
-// minmod(a,b) = sgn(a) max(0, min(|a|, sgn(a) b))  (eq. minmod)
+// minmod(a,b) = sgn(a) max(0, min(|a|, sgn(a) b))  (eq. minmod), as the
+// smaller of two positive values plus the larger of two negative ones (one of
+// the two terms is zero): five FP64 instructions where the sign, its products
+// and their selects took about fifteen
 template <typename T>
 __device__ __forceinline__ T lim_minmod(T a, T b)
 {
-    T s = sgn_of(a);
-    T m = fabs(a);
-    T t = s * b;
-    m = t < m ? t : m;
-    m = m < T(0) ? T(0) : m;
-    return s * m;
+    return Num<T>::max_(Num<T>::min_(a, b), T(0)) + Num<T>::min_(Num<T>::max_(a, b), T(0));
 }
 
 // in FP32 the same value is the median of (a, b, 0): the smaller magnitude
@@ -103,7 +109,7 @@ struct Phys {
                         (double)u[MZ] * (double)u[MZ];
             double b2 = (double)u[BX] * (double)u[BX] + (double)u[BY] * (double)u[BY] +
                         (double)u[BZ] * (double)u[BZ];
-            return (T)(gm1d * (((double)u[EN] - 0.5 * m2 * r) - 0.5 * b2));
+            return (T)(gm1d * ((double)u[EN] - 0.5 * (m2 * r + b2)));
         } else {
             T ke = T(0.5) * (u[MX] * vx + u[MY] * vy + u[MZ] * vz);
             return gm1 * (u[EN] - ke - me);
@@ -223,11 +229,9 @@ __device__ __forceinline__ T fast_sel(const T u[NV], const Prim<T> &w, int d, T 
     const T b2 = w.bb * w.ir;
     const T s = a2 + b2;
     const T Bd = d == 0 ? u[BX] : (d == 1 ? u[BY] : u[BZ]);
-    T disc = s * s - T(4) * a2 * (Bd * Bd) * w.ir;
-    disc = disc < T(0) ? T(0) : disc;
-    T cf2 = T(0.5) * (s + Num<T>::sqrt_(disc));
-    cf2 = cf2 < T(0) ? T(0) : cf2;
-    return Num<T>::sqrt_(cf2);
+    const T disc = Num<T>::max_(s * s - T(4) * a2 * (Bd * Bd) * w.ir, T(0));
+    const T cf2 = T(0.5) * (s + Num<T>::sqrt_(disc));
+    return Num<T>::sqrt_(Num<T>::max_(cf2, T(0)));
 }
 
 // |v_d| + c_f,d from a state and its primitives (d as in flux_sel)

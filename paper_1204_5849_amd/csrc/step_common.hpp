@@ -11,9 +11,11 @@ namespace mapk {
 // (Sec. 3.3, component-wise, third order): L = u^-_{i+1/2} and
 // R = u^+_{i-1/2}.  The smoothness weights are a = 1/s^2 with
 // s = eps + (difference)^2, eps = 1e-12; multiplying numerator and
-// denominator by s_-^2 s_+^2 leaves one division per state:
-//   L = (2 s_-^2 w + s_+^2 v) / (2 s_-^2 + s_+^2),  w = (u0 + up)/2, v = (3 u0 - um)/2
-//   R = (s_-^2 w' + 2 s_+^2 v') / (s_-^2 + 2 s_+^2), w' = (3 u0 - up)/2, v' = (u0 + um)/2
+// denominator by s_-^2 s_+^2 leaves one division per state, and with the
+// differences d_- = u0 - um, d_+ = up - u0 the stencil values are u0 + d_+/2
+// and u0 + d_-/2 (u0 - d_-/2 and u0 - d_+/2 on the other side), so
+//   L = u0 + (2 s_-^2 d_+ + s_+^2 d_-) / (2 (2 s_-^2 + s_+^2))
+//   R = u0 - (s_-^2 d_+ + 2 s_+^2 d_-) / (2 (s_-^2 + 2 s_+^2)).
 // In FP32 both s are first scaled by one power of two (exact), so that their
 // squares neither overflow nor both underflow.
 template <typename T>
@@ -22,14 +24,14 @@ __device__ __forceinline__ void weno_pair(T um, T u0, T up, T &L, T &R)
     const T dm = u0 - um, dp = up - u0;
     T sm = T(1e-12) + dm * dm, sp = T(1e-12) + dp * dp;
     if constexpr (sizeof(T) == 4) {
-        const int e = __builtin_amdgcn_frexp_expf(sm > sp ? sm : sp);
+        const int e = __builtin_amdgcn_frexp_expf(Num<T>::max_(sm, sp));
         sm = __builtin_amdgcn_ldexpf(sm, -e);
         sp = __builtin_amdgcn_ldexpf(sp, -e);
     }
-    const T qm = sm * sm, qp = sp * sp;
+    const T qm = sm * sm, qp = sp * sp, am = qm + qm, ap = qp + qp;
     const T h = T(0.5);
-    L = Num<T>::div(T(2) * qm * (h * (u0 + up)) + qp * (h * (T(3) * u0 - um)), T(2) * qm + qp);
-    R = Num<T>::div(qm * (h * (T(3) * u0 - up)) + T(2) * qp * (h * (u0 + um)), qm + T(2) * qp);
+    L = u0 + h * Num<T>::div(am * dp + qp * dm, am + qp);
+    R = u0 - h * Num<T>::div(qm * dp + ap * dm, qm + ap);
 }
 
 // Rusanov flux (Equ:LFFlux) across a face normal to dimension d, with alpha
@@ -57,7 +59,7 @@ __device__ __forceinline__ void rusanov_sel(const T L[NV], T pL, const T R[NV], 
     flux_sel(L, wL, d, ch2, FL);
     flux_sel(R, wR, d, ch2, FR);
     const T sL = speed_sel(L, wL, d, gamma), sR = speed_sel(R, wR, d, gamma);
-    const T al = sL > sR ? sL : sR;
+    const T al = Num<T>::max_(sL, sR);
 #pragma unroll
     for (int k = 0; k < NV; k++) {
         const T ak = (k == BX + d || k == PSI) ? ch : al;
@@ -141,15 +143,18 @@ __device__ __forceinline__ void hllc_sel(const T L0[NV], T pL0, const T R0[NV], 
         const T ps1 = U[1][RHO] * (SR - v[1]) * (SM - v[1]) + pt[1];
         const T pst = h * (ps0 + ps1);
         const bool right = SM < T(0);
-        const T S = right ? SR : SL;
-        const T vs = right ? v[1] : v[0];
-        const T pts = right ? pt[1] : pt[0];
-        const T vbs = right ? vb[1] : vb[0];
+        // (bit selects: a run of v_cndmask on one condition issues at about
+        // 20 cycles each, v_bfi at 4)
+        const unsigned m = right ? ~0u : 0u;
+        const T S = Num<T>::pick(m, SR, SL);
+        const T vs = Num<T>::pick(m, v[1], v[0]);
+        const T pts = Num<T>::pick(m, pt[1], pt[0]);
+        const T vbs = Num<T>::pick(m, vb[1], vb[0]);
         T us[NV], fs[NV];
 #pragma unroll
         for (int k = 0; k < NV; k++) {
-            us[k] = right ? U[1][k] : U[0][k];
-            fs[k] = right ? F[1][k] : F[0][k];
+            us[k] = Num<T>::pick(m, U[1][k], U[0][k]);
+            fs[k] = Num<T>::pick(m, F[1][k], F[0][k]);
         }
         const T sv = S - vs;
         const T iden = Num<T>::rcp(S - SM);
