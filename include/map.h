@@ -300,9 +300,8 @@ typedef struct {
     int grid_fill;       /* the same for the parent-frame copies of the fill */
     int step_shape;      /* workgroup shape of the update: 2-D LF and WENO,
                             0 = 14 blocks in 4 waves, 1 = 7 blocks in 2 waves;
-                            3-D FP32 LF and WENO, 0 = compiled for two
-                            workgroups per CU (256 registers per lane), 1 =
-                            for one (512); 0 elsewhere */
+                            3-D FP32 LF and WENO, 0 or 1 = two settings of
+                            the waves' issue priorities; 0 elsewhere */
     int restrict_split;  /* restriction levels with fewer parents than this
                             take one workgroup per child, the others one per
                             parent; -1 = the number of compute units */

@@ -307,6 +307,7 @@ map_status run_step_kernel(map_ctx *c, int sch, const void *Uin, void *Uout, con
     a.limiter = c->p.limiter;
     a.riemann = c->p.riemann;
     a.shape = c->step_shape;
+    a.ncu = c->ncu;
     a.cfl_on = cfl_next && cfl_in_update(c);
     a.cfl_leaf = dptr<int32_t>(c, c->ws.cfl_leaf);
     a.cfl_part = dptr<double>(c, c->ws.cfl_part);

@@ -1,14 +1,13 @@
 // k_step3.hpp -- the block update of 3-D leaf blocks: the TVD-LF step
 // (paper Sec. 3.2) or one stage of WENO with TVD Runge-Kutta 2 (Sec. 3.3),
 // all directions together (Sec. 3.7), with the EGLM source terms (Sec. 2),
-// uniform resistivity (Sec. 3.5) and exact psi damping.
+// uniform resistivity (Sec. 3.5) and exact psi damping.  FP32 runs the
+// wave-split update of k_step3d.hpp; this file holds the FP64 one and the
+// kernel template.
 //
-// Schedule (gfx950): one block per workgroup of 4 waves, so that two
-// workgroups share a compute unit (the FP32 kernel keeps to 256 registers
-// and 80 KB of LDS per workgroup) and one block's waits overlap the other's
-// arithmetic; an FP32 instance compiled for one workgroup per CU (512
-// registers, no spills) is the launch autotuner's alternative.  Threads own the 16 x 16 interior columns of the block and
-// march along z one plane per iteration:
+// Schedule (gfx950): one block per workgroup of 4 waves and one workgroup per
+// CU (455-466 registers, 153 KB of LDS).  Threads own the 16 x 16 interior
+// columns of the block and march along z one plane per iteration:
 //   * march-axis neighbours (slopes, the half-step flux, the face between
 //     planes, source and resistive differences) stay in the thread's
 //     registers; in-plane neighbours are exchanged through LDS one plane at
@@ -40,10 +39,9 @@
 //     stores u1 without damping, stage 2 stores (u + u1 + dt L(u1)) / 2, u
 //     read from U_base at the cell itself, then damps psi, and the reflux
 //     face fluxes become the mean of both stages' fluxes.
-// A persistent grid strides over the leaf list.  The FP32 resistive LF and
-// first WENO stage instances are compiled in k_step3_ilp.hip, the others in
-// k_step3.hip: they take different instruction schedulers (see the build
-// script).
+// A persistent grid strides over the leaf list.  The FP32 LF instances are
+// compiled in k_step3_ilp.hip, the others in k_step3.hip: they take different
+// compiler options (see the build script).
 #pragma once
 
 #include <type_traits>
@@ -53,6 +51,7 @@
 #include "step_common.hpp"
 #include "sched.hpp"
 #include "tile.hpp"
+#include "k_step3d.hpp"
 
 namespace mapk {
 
@@ -67,8 +66,8 @@ constexpr int OPW = NOUT / 4;         // outer cells per wave (20)
 static_assert(NB == 16 && NT3 == 256, "lane layout assumes 16^3 blocks");
 }  // namespace
 
-template <typename T, bool MIXED, bool RESIST, int SCH, int LIM, int RS, int OCC>
-__global__ void __launch_bounds__(NT3, OCC) k_step3(StepArgs a)
+template <typename T, bool MIXED, bool RESIST, int SCH, int LIM, int RS>
+__device__ __forceinline__ void step3_columns(const StepArgs &a)
 {
     constexpr int SY = PD;
     constexpr int SUB = NV * XS3;
@@ -776,21 +775,75 @@ __global__ void __launch_bounds__(NT3, OCC) k_step3(StepArgs a)
     }
 }
 
-// FP32: compiled for two workgroups per CU (shape 0) or one (shape 1, twice
-// the registers); FP64 (148 KB of LDS) for one
+// FP32: the dimensions on three threads (k_step3d.hpp); FP64, whose planes
+// leave no room in LDS for that (three planes of state alone are 86 KB), one
+// thread per column.  SHAPE (FP32): the issue priorities of the x and y waves
+// (z waves 0, ring waves 3).  The y waves carry the most work per plane and the
+// ring waves share three of the four SIMDs with a wave of each dimension, so
+// both go first.
+// (The role dispatch stays in the kernel body: inside a called function the
+// compiler kept the roles' addresses live across each other, 163 registers
+// spilled instead of 10.)
+template <typename T, bool MIXED, bool RESIST, int SCH, int LIM, int RS, int SHAPE>
+__global__ void __launch_bounds__(sizeof(T) == 4 ? NTD : NT3) k_step3(StepArgs a)
+{
+    if constexpr (sizeof(T) == 4) {
+        using M = March3d<T, MIXED, RESIST, SCH, LIM, RS, SHAPE>;
+        __shared__ typename M::Sh sh;
+        const int t = threadIdx.x;
+        const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
+        const bool ring = wv >= 12;
+        constexpr bool HIGH = (SCH == SCH_LF) == (SHAPE == 0);
+        const int role = ring ? 3 : wv >> 2;
+        if (role == 0)
+            __builtin_amdgcn_s_setprio(HIGH ? 2 : 1);
+        else if (role == 1)
+            __builtin_amdgcn_s_setprio(HIGH ? 3 : 2);
+        else if (role == 3)
+            __builtin_amdgcn_s_setprio(3);
+        // neighbouring blocks on one XCD, so that the ghost cells read from
+        // neighbours come from that XCD's L2
+        int first, stride, end;
+        xcd_range(a.nitems, first, stride, end);
+        for (int item = first; item < end; item += stride) {
+            const int slot = a.leaves[item];
+            if (ring) {
+                if (wv == 12)
+                    M::template run<0, true>(a, sh, slot, t);
+                else if (wv == 13)
+                    M::template run<1, true>(a, sh, slot, t);
+                else
+                    M::template run<2, true>(a, sh, slot, t);
+            } else if (wv < 4) {
+                M::template run<0, false>(a, sh, slot, t);
+            } else if (wv < 8) {
+                M::template run<1, false>(a, sh, slot, t);
+            } else {
+                M::template run<2, false>(a, sh, slot, t);
+            }
+        }
+    } else {
+        step3_columns<T, MIXED, RESIST, SCH, LIM, RS>(a);
+    }
+}
+
 template <typename T, bool MIXED, bool RESIST, int SCH, int LIM, int RS>
 static hipError_t launch3(const StepArgs &a, int grid, hipStream_t s)
 {
+    // one FP32 workgroup fills a CU: by default a persistent grid of one per
+    // CU (1510 -> 1526 us with one per leaf)
+    if (grid <= 0 && sizeof(T) == 4)
+        grid = a.ncu;
     const int g = grid > 0 ? (grid < a.nitems ? grid : a.nitems) : a.nitems;
     if constexpr (sizeof(T) == 4) {
         if (a.shape == 1)
-            hipLaunchKernelGGL((k_step3<T, MIXED, RESIST, SCH, LIM, RS, 1>), dim3(g), dim3(NT3), 0,
+            hipLaunchKernelGGL((k_step3<T, MIXED, RESIST, SCH, LIM, RS, 1>), dim3(g), dim3(NTD), 0,
                                s, a);
         else
-            hipLaunchKernelGGL((k_step3<T, MIXED, RESIST, SCH, LIM, RS, 2>), dim3(g), dim3(NT3), 0,
+            hipLaunchKernelGGL((k_step3<T, MIXED, RESIST, SCH, LIM, RS, 0>), dim3(g), dim3(NTD), 0,
                                s, a);
     } else {
-        hipLaunchKernelGGL((k_step3<T, MIXED, RESIST, SCH, LIM, RS, 1>), dim3(g), dim3(NT3), 0, s, a);
+        hipLaunchKernelGGL((k_step3<T, MIXED, RESIST, SCH, LIM, RS, 0>), dim3(g), dim3(NT3), 0, s, a);
     }
     return hipGetLastError();
 }

@@ -1,32 +1,30 @@
-// k_step3_ilp.hip -- the FP32 resistive instances of the 3-D block update
-// that run faster under LLVM's ILP-first instruction scheduler: the TVD-LF
-// step (one per limiter and face flux) and the first WENO stage.  The
-// others stay in k_step3.hip with the default scheduler (see the build
-// script).
+// k_step3_ilp.hip -- the FP32 instances of the 3-D TVD-LF step (one per limiter
+// and face flux, with and without resistivity).  They run faster without
+// LLVM's loop strength reduction, whose per-variable address registers spill
+// at 128 registers per lane; the others stay in k_step3.hip with the defaults
+// (see the build script).
 #include "k_step3.hpp"
 
 namespace mapk {
 
-template <int RS>
-static hipError_t launch3_ilp(int sch, const StepArgs &a, int grid, hipStream_t s)
+template <bool RESIST, int RS>
+static hipError_t launch3_lf32(const StepArgs &a, int grid, hipStream_t s)
 {
-    if (sch == SCH_WENO1)
-        return launch3<float, true, true, SCH_WENO1, MAP_MINMOD, RS>(a, grid, s);
     if (a.limiter == MAP_MINMOD)
-        return launch3<float, true, true, SCH_LF, MAP_MINMOD, RS>(a, grid, s);
+        return launch3<float, true, RESIST, SCH_LF, MAP_MINMOD, RS>(a, grid, s);
     if (a.limiter == MAP_VANLEER)
-        return launch3<float, true, true, SCH_LF, MAP_VANLEER, RS>(a, grid, s);
-    return launch3<float, true, true, SCH_LF, MAP_PAPER_PHI, RS>(a, grid, s);
+        return launch3<float, true, RESIST, SCH_LF, MAP_VANLEER, RS>(a, grid, s);
+    return launch3<float, true, RESIST, SCH_LF, MAP_PAPER_PHI, RS>(a, grid, s);
 }
 
-// FP32, resistive, LF or the first WENO stage
-hipError_t launch_step3_ilp(int sch, const StepArgs &a, int grid, hipStream_t s)
+hipError_t launch_step3_lf32(bool resist, const StepArgs &a, int grid, hipStream_t s)
 {
     if (a.nitems <= 0)
         return hipSuccess;
     if (a.riemann == MAP_HLLC)
-        return launch3_ilp<MAP_HLLC>(sch, a, grid, s);
-    return launch3_ilp<MAP_RUSANOV>(sch, a, grid, s);
+        return resist ? launch3_lf32<true, MAP_HLLC>(a, grid, s) : launch3_lf32<false, MAP_HLLC>(a, grid, s);
+    return resist ? launch3_lf32<true, MAP_RUSANOV>(a, grid, s)
+                  : launch3_lf32<false, MAP_RUSANOV>(a, grid, s);
 }
 
 }  // namespace mapk

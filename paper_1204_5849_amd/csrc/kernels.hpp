@@ -31,9 +31,9 @@ struct StepArgs {
     double gamma, eta;
     int eglm, limiter, riemann;
     // workgroup shape of the update: 2-D LF / WENO, 0 = 14 blocks in 4 waves,
-    // 1 = 7 blocks in 2 waves; 3-D FP32 LF / WENO, 0 = compiled for two
-    // workgroups per CU (256 registers per lane), 1 = for one (512)
+    // 1 = 7 blocks in 2 waves; 3-D FP32 LF / WENO, the wave priorities (0, 1)
     int shape;
+    int ncu;                // compute units
     // 2-D LF: with cfl_on, the next cycle's CFL maximum of each leaf whose
     // cfl_leaf[slot] >= 0 (a leaf without parent that no reflux changes) is
     // formed from the values the update writes, into cfl_part[cfl_leaf[slot]]
@@ -179,7 +179,7 @@ struct RemapArgs {
 // launchers (defined in the .hip files); return hipError_t of the launch
 hipError_t launch_step2(bool fp64, bool resist, int sch, const StepArgs &a, int grid, hipStream_t s);
 hipError_t launch_step3(bool fp64, bool resist, int sch, const StepArgs &a, int grid, hipStream_t s);
-hipError_t launch_step3_ilp(int sch, const StepArgs &a, int grid, hipStream_t s);
+hipError_t launch_step3_lf32(bool resist, const StepArgs &a, int grid, hipStream_t s);
 hipError_t launch_step_mmc(int ndim, bool fp64, const StepArgs &a, double alpha_unused, int grid,
                            hipStream_t s);
 hipError_t launch_step_mmc3(bool fp64, bool resist, const StepArgs &a, int grid, hipStream_t s);
