@@ -256,3 +256,15 @@ def test_run_adaptive_equals_manual_regrids(dev):
         ptrs.append(a._ubuf.data_ptr())
     a.regrid_in_place(CRIT, tr, tc, 3)
     assert a._ubuf.data_ptr() == ptrs[0]
+
+
+@pytest.mark.parametrize("name,precision", [("ot", "fp64"), ("blast", "fp32"), ("harris", "fp64")])
+def test_criteria_together_equal_criteria_alone(dev, name, precision):
+    """1 to 4 criteria in one pass: the maximum of the passes of each alone, bit for bit."""
+    w = _tree2d(precision) if name == "ot" else _workload(name, precision)
+    s = _sim(w)
+    s.advance(2)
+    crit = [("bmag", 0, 0.1), ("var", 7, 1e-12), ("var", 1, 0.3), ("var", 0, 1e-12)]
+    alone = [s.estimate([c], xi=0.5) for c in crit]
+    for n in range(2, 5):
+        assert np.array_equal(s.estimate(crit[:n], xi=0.5), np.maximum.reduce(alone[:n]))
