@@ -127,6 +127,9 @@ map_status run_fill(map_ctx *c, void *U, hipStream_t s, bool all, int eonly_sub 
             a.nitems = 1;
             HIPCHK(launch_fill_copy(c->nd, fp64(c), a, 1, s));
         }
+    } else if (all && c->nd == 3) {
+        a.slot_end = ncopy;
+        HIPCHK(launch_fill_all3(fp64(c), a, c->ncu, s));
     } else if (ncopy > 0) {
         a.slot_base = 0;
         a.slot_end = ncopy;

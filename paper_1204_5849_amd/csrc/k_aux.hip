@@ -152,6 +152,130 @@ __global__ void __launch_bounds__(NTA) k_fill_copy(FillArgs a)
     }
 }
 
+// ---- the complete ghost frames of every 3-D block (copies), one variable of
+// a block per item.  x ghosts take 16 bytes of every line of both x neighbours,
+// so a block per item fetched each state line several times (14.3 GB for a
+// 6.3 GB state: the 256 blocks in flight on an XCD do not fit its L2).  A
+// chunk of neighbouring blocks is walked one variable at a time instead,
+// whose tiles do fit: 11.5 GB, and 3612 -> 3291 us for the
+// 22016-block FP32 state, 1715 -> 1509 us for 5440 FP64 blocks, 275 -> 250 us
+// for 1024 FP32 blocks.  Chunks of 16 and 64 blocks take 3303 and 3358 us,
+// 2 or 8 workgroups per CU 3705 and 3613, stores from the block that holds the
+// values into its neighbours' frames (whole lines read, pieces stored) 4890.
+// Bound by the pieces of lines it moves: 16-byte x ghosts in 11.5 GB read and
+// 4.3 GB written for 3.1 GB of ghosts.
+// The cells' order and offsets are the same for every block: a table in LDS
+// gives the g-th ghost cell in address order (so the two cells after a row and
+// the two before the next one are one 4-cell run) and its region, and per item
+// 125 lanes turn the descriptors into one source offset per region (five per
+// dimension: -2, -1, the interior, 16, 17).
+template <typename T>
+__global__ void __launch_bounds__(NTA) k_fill_all(FillArgs a)
+{
+    constexpr int P = FG<3>::P, NGC = FG<3>::NGC, NREG = 125;
+    constexpr int CH = sizeof(T) == 4 ? 32 : 16;  // blocks per chunk
+    constexpr long long NONE = -(1ll << 62);
+    __shared__ uint32_t tab[NGC];        // region << 13 | linear index
+    __shared__ long long base[2][NREG];  // by item parity
+    T *U = (T *)a.U;
+    const int t = threadIdx.x;
+    for (int g = t; g < NGC; g += NTA) {
+        int c, z;
+        if (g < 2 * PD * PD) {
+            z = g / (PD * PD);
+            c = g % (PD * PD);
+        } else if (g < 2 * PD * PD + NB * (PD * PD - NB * NB)) {
+            constexpr int Q = PD * PD - NB * NB;  // 144: 42, then 15 runs of 4, then 42
+            z = (g - 2 * PD * PD) / Q + NG;
+            const int h = (g - 2 * PD * PD) % Q;
+            c = h < 42 ? h : (h < 102 ? 58 + PD * ((h - 42) / 4) + (h - 42) % 4 : 358 + h - 102);
+        } else {
+            const int h = g - 2 * PD * PD - NB * (PD * PD - NB * NB);
+            z = NB + NG + h / (PD * PD);
+            c = h % (PD * PD);
+        }
+        auto reg = [](int p) { return p < NG ? p : (p < NB + NG ? 2 : p - NB + 1); };
+        tab[g] = (uint32_t)((reg(z) * 5 + reg(c / PD)) * 5 + reg(c % PD)) << 13 | (uint32_t)(z * PD * PD + c);
+    }
+    // this XCD's blocks, their items walked by its workgroups
+    const int G = gridDim.x, x = blockIdx.x & 7, l = blockIdx.x >> 3;
+    const int full = G >> 3, rem = G & 7, cnt = full + (x < rem ? 1 : 0);
+    const int before = x * full + (x < rem ? x : rem);
+    const int lo = (int)((long long)a.slot_end * before / G),
+              hi = (int)((long long)a.slot_end * (before + cnt) / G);
+    const int n = (hi - lo) * NV;
+    auto decode = [&](int j, int &slot, int &v) {
+        const int c0 = j / (CH * NV), r = j - c0 * (CH * NV);
+        const int nb = hi - lo - c0 * CH < CH ? hi - lo - c0 * CH : CH;
+        v = r / nb;
+        slot = lo + c0 * CH + r - v * nb;
+    };
+    // source of region t of a block, less the cell's own linear index
+    auto set_base = [&](int slot, int v, int par) {
+        if (t >= NREG)
+            return;
+        const int r[3] = {t % 5, (t / 5) % 5, t / 25};
+        int di = 0;
+        const int w[3] = {1, 3, 9}, st[3] = {1, PD, PD * PD};
+#pragma unroll
+        for (int d = 0; d < 3; d++)
+            di += w[d] * (r[d] < 2 ? 0 : (r[d] == 2 ? 1 : 2));
+        const Desc ds = a.desc[(size_t)slot * NDIR + di];
+        if (ds.src < 0) {
+            base[par][t] = NONE;
+            return;
+        }
+        const int o[3] = {ds.o0, ds.o1, ds.o2};
+        int shift = 0;
+#pragma unroll
+        for (int d = 0; d < 3; d++) {
+            const int g = r[d] < 2 ? r[d] - NG : (r[d] == 2 ? 0 : r[d] + NB - 3);  // ghost index
+            shift += (src_index(g, o[d]) - g) * st[d];
+        }
+        base[par][t] = ((long long)ds.src * NV + v) * P + shift;
+    };
+    int slot = 0, v = 0;
+    if (l < n) {
+        decode(l, slot, v);
+        set_base(slot, v, 0);
+    }
+    __syncthreads();
+    int par = 0;
+    for (int j = l; j < n; j += cnt, par ^= 1) {
+        T *dst = U + ((size_t)slot * NV + v) * P;
+        int slot2 = 0, v2 = 0;
+        if (j + cnt < n) {
+            decode(j + cnt, slot2, v2);
+            set_base(slot2, v2, par ^ 1);
+        }
+        constexpr int K = 4;  // cells in flight per lane
+        for (int g0 = t; g0 < NGC; g0 += K * NTA) {
+            T val[K];
+            int at[K];
+#pragma unroll
+            for (int k = 0; k < K; k++) {
+                const int g = g0 + k * NTA;
+                at[k] = -1;
+                if (g < NGC) {
+                    const uint32_t e = tab[g];
+                    const long long b = base[par][e >> 13];
+                    if (b != NONE) {
+                        at[k] = (int)(e & 8191u);
+                        val[k] = U[b + at[k]];
+                    }
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < K; k++)
+                if (at[k] >= 0)
+                    dst[at[k]] = val[k];
+        }
+        slot = slot2;
+        v = v2;
+        __syncthreads();
+    }
+}
+
 // minmod-limited linear interpolation from the parent's padded tile at fine
 // padded cell (x, y, z) of a child in position cpos (Sec. 4.3, step 6)
 template <int NDIM, typename T, int K0 = 0, int K1 = NV>
@@ -875,6 +999,19 @@ hipError_t launch_fill_copy(int ndim, bool fp64, const FillArgs &a, int grid, hi
     if (a.eonly && g > SUB_GRID)
         g = SUB_GRID;
     DISPATCH_EO(ndim, fp64, a.eonly, k_fill_copy, dim3(g), dim3(NTA), 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_fill_all3(bool fp64, const FillArgs &a, int ncu, hipStream_t s)
+{
+    if (a.slot_end <= 0)
+        return hipSuccess;
+    const int items = a.slot_end > 1 << 26 ? 1 << 30 : a.slot_end * NV;
+    const int g = 4 * ncu < items ? 4 * ncu : items;
+    if (fp64)
+        hipLaunchKernelGGL(k_fill_all<double>, dim3(g), dim3(NTA), 0, s, a);
+    else
+        hipLaunchKernelGGL(k_fill_all<float>, dim3(g), dim3(NTA), 0, s, a);
     return hipGetLastError();
 }
 

@@ -186,6 +186,7 @@ hipError_t launch_step_mmc3(bool fp64, bool resist, const StepArgs &a, int grid,
 // blocks per workgroup of the batched update for a workgroup shape (StepArgs::shape)
 int step_blocks_per_group(int ndim, int scheme, int shape);
 hipError_t launch_fill_copy(int ndim, bool fp64, const FillArgs &a, int grid, hipStream_t s);
+hipError_t launch_fill_all3(bool fp64, const FillArgs &a, int ncu, hipStream_t s);
 hipError_t launch_prolong_ghosts(int ndim, bool fp64, const FillArgs &a, hipStream_t s);
 hipError_t launch_prolong_blocks(int ndim, bool fp64, const FillArgs &a, hipStream_t s);
 hipError_t launch_restrict(int ndim, bool fp64, const RestrictArgs &a, hipStream_t s);

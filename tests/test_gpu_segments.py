@@ -109,3 +109,40 @@ def test_short_and_long_lists_3d(scheme, precision):
         a, b, t = run(tree(copies))
         assert np.array_equal(a, one) and np.array_equal(b, one), copies
         assert np.array_equal(t, np.repeat(tot, copies, axis=0))
+
+
+@pytest.mark.parametrize("copies,precision", [(1, "fp64"), (1, "fp32"), (25, "fp64"), (25, "fp32"),
+                                              (300, "fp32")])
+def test_complete_frames_3d(copies, precision):
+    """The ghost frames of every block (outflow and periodic edges, prolongated
+    ghosts, parents): one variable of a block per item over chunks of blocks,
+    against one launch per block, bit for bit.  16 blocks (144 items, 2 per
+    XCD), 400 blocks (50 per XCD: chunks of 32 and 16 with a remainder) and
+    4800 blocks."""
+    sd = W.SimDesc(lo=(0, 0, 0), hi=(1, 1, 1), nbase=(2, 2, 2),
+                   bc=(("outflow", "outflow"), ("periodic",) * 2, ("outflow",) * 2))
+    keys = []
+    for s in range(copies):
+        base = W.base_keys(s, sd.nbase, 3)
+        keys += [base, W.children_of(base[3:4], 3)]
+    w = W.Workload(name="frames", ndim=3, sims=[sd] * copies, keys=np.concatenate(keys), ic=_ic,
+                   scheme="lf", precision=precision, glm_mode="fastspeed")
+    s = Simulation(w, device="cuda:0")
+    s.load_initial()
+    s.U += torch.rand(s.U.shape, device=s.device, dtype=torch.float64,
+                      generator=torch.Generator(s.device).manual_seed(5)).to(s.U.dtype)
+    torch.cuda.synchronize()
+    ghosts = torch.ones_like(s.U, dtype=torch.bool)
+    ghosts[:, :, 2:-2, 2:-2, 2:-2] = False
+    base = s.U.clone()
+    out = []
+    for mode in (N.MAP_LAUNCH_BATCHED, N.MAP_LAUNCH_PER_BLOCK):
+        s.U.copy_(base)
+        s.U.masked_fill_(ghosts, float("nan"))
+        torch.cuda.synchronize()
+        s.set_launch(mode)
+        s.fill()
+        s.sync()
+        out.append(s.U.clone())
+    assert not out[0].isnan().any()
+    assert torch.equal(out[0], out[1])
