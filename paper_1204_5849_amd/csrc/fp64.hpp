@@ -47,4 +47,10 @@ __device__ __forceinline__ double sqrt64(double x)
     return __builtin_amdgcn_div_fixup(g, 1.0, x);
 }
 
+// any x: NaN below zero, minus infinity included
+__device__ __forceinline__ double sqrt64_any(double x)
+{
+    return x < 0.0 ? __builtin_nan("") : sqrt64(x);
+}
+
 }  // namespace mapk

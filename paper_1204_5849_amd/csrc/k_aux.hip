@@ -739,7 +739,7 @@ __global__ void __launch_bounds__(NT) k_cfl(CflArgs a)
                 bad++;
             if (a.cpart) {
                 // conduction: kappa T / p = kappa / rho with T = p / rho
-                const double r = kappa_of(a.kappa0, a.khalf, pr / u[RHO]) / u[RHO];
+                const double r = div64(kappa_of(a.kappa0, a.khalf, div64(pr, u[RHO])), u[RHO]);
                 cm = r > cm ? r : cm;
             }
             m = s > m ? s : m;

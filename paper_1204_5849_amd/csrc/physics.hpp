@@ -52,7 +52,7 @@ __device__ __forceinline__ double kappa_of(double kappa0, int khalf, double T)
     for (int i = 0; i < khalf / 2; i++)
         q = q * T;
     if (khalf & 1)
-        q = q * sqrt(T);
+        q = q * sqrt64_any(T);
     return kappa0 * q;
 }
 
