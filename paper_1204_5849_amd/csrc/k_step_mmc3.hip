@@ -9,7 +9,12 @@
 // Sec. 3.5) and the exact psi damping.
 //
 // One block per workgroup of 4 waves, marching along z one plane per
-// iteration.  Thread t owns the interior column (t % 16, t / 16); lanes 0-15
+// iteration; the blocks that would leave the last round of workgroups nearly
+// empty are cut into segments along z, each of which passes over the planes
+// next to it as well (without their x and y faces): 288 FP64
+// leaves on 256 CUs took two full rounds, 568 us, and take 337.
+// Bound by instruction issue and LDS reads on one (FP64) or two (FP32) waves
+// per SIMD with ten barriers a plane.  Thread t owns the interior column (t % 16, t / 16); lanes 0-15
 // of wave w also own the ring cell of side w (x = -1, x = 16, y = -1,
 // y = 16) and lanes 16-35 the outer cells of the padded plane, as in the LF
 // kernel.  Per plane p:
@@ -46,13 +51,25 @@ constexpr int NOM = 4 * PD;           // outer ring and ring corners
 constexpr int OPWM = NOM / 4;         // outer cells per wave (20)
 constexpr int NLDM = NRM + NOM;       // cells with a load role
 constexpr int NFACE = (NB + 1) * NB;  // in-plane faces of one dimension (272)
+constexpr int MAXSEG = 3;             // log2 of the most march segments of a block (2 planes)
+
+// workgroups per CU: LDS holds one FP64 block (143 KB, 156 KB with
+// resistivity) or two FP32 blocks, at 256 registers (1297 -> 840 us for 1464
+// leaves against one per CU, though 52 are spilled, 1107 -> 1072 us for 1176
+// leaves with resistivity)
+constexpr int per_cu(size_t word) { return word == 4 ? 2 : 1; }
+// and resident ones per XCD
+__host__ __device__ inline int march_slots(int ncu, size_t word)
+{
+    return (ncu >= 8 ? ncu / 8 : 1) * per_cu(word);
+}
 
 __device__ __forceinline__ int pl(int x, int y) { return (y + NG) * PD + (x + NG); }
 __device__ __forceinline__ int ei(int x, int y) { return (y + 1) * EW + (x + 1); }
 }  // namespace
 
 template <typename T, bool MIXED, bool RESIST, int LIM>
-__global__ void __launch_bounds__(NTM) k_step_mmc3(StepArgs a)
+__global__ void __launch_bounds__(NTM, per_cu(sizeof(T))) k_step_mmc3(StepArgs a)
 {
     __shared__ T su[NV * XSM];           // u of plane p (padded plane)
     __shared__ T sF[NV * XSM];           // F_d(u(p)) of one dimension (padded plane)
@@ -60,7 +77,7 @@ __global__ void __launch_bounds__(NTM) k_step_mmc3(StepArgs a)
     __shared__ T sft[NV * XE];           // F_d(u~(p)) of one dimension (E plane)
     __shared__ T sfh[NV * NFACE];        // in-plane face fluxes of one dimension
     __shared__ T sring[3 * NV * NRM];    // ring cells of planes p-1, p, p+1
-    __shared__ T sj[RESIST ? 5 * XSM : 1];  // eta J and eta (J x B) of plane p
+    __shared__ T sj[RESIST ? 5 * XE : 1];  // eta J and eta (J x B) of plane p (E plane)
     __shared__ size_t gld[5 * NLDM];     // load roles: source offsets per plane region
 
     const int t = threadIdx.x;
@@ -110,10 +127,14 @@ __global__ void __launch_bounds__(NTM) k_step_mmc3(StepArgs a)
     constexpr int P3 = XSM * PD;
     constexpr int FC = NB * NB;
 
-    int first, stride, end;
-    xcd_range(a.nitems, first, stride, end);
-    for (int item = first; item < end; item += stride) {
-        const int slot = a.leaves[item];
+    int first, stride;
+    const Marches mar = xcd_marches(a.nleaves, march_slots(a.ncu, sizeof(T)), MAXSEG, first, stride);
+    for (int item = first; item < mar.n; item += stride) {
+        int seg, lseg;
+        const int slot = a.leaves[march_item(mar, item, seg, lseg)];
+        // the planes of this item: it marches from the one below them to the
+        // one above, whose x and y faces it does not need
+        const int z0 = seg * (NB >> lseg), z1 = z0 + (NB >> lseg);
         const BlockRec br = a.blk[slot];
         const map_dt rec = a.dt[br.sim];
         const double *dxp = a.lvl_dx + ((size_t)br.sim * (MAXL + 1) + br.level) * 3;
@@ -160,21 +181,30 @@ __global__ void __launch_bounds__(NTM) k_step_mmc3(StepArgs a)
         };
         auto rslot = [&](int k) { return sring + ((k + 6) % 3) * (NV * NRM); };
 
-        // split fluxes of a state along D
-        auto split = [&](auto dc, const T u[NV], T (&fp)[NV], T (&fm)[NV]) {
-            constexpr int D = decltype(dc)::value;
+        // split fluxes of a state along z, with the contractions written out:
+        // the compiler's own differ between the march's first planes and the
+        // others, and the bits would depend on where a segment starts
+        auto split_z = [&](const T u[NV], T (&fp)[NV], T (&fm)[NV]) {
+#pragma clang fp contract(off)
             T F[NV];
-            ph.template flux<D, false>(u, ch2, F);
+            ph.flux_z(u, ch2, F);
 #pragma unroll
             for (int v = 0; v < NV; v++) {
-                fp[v] = T(0.5) * (F[v] + al(v, D) * u[v]);
-                fm[v] = T(0.5) * (F[v] - al(v, D) * u[v]);
+                fp[v] = T(0.5) * Num<T>::fma_(al(v, 2), u[v], F[v]);
+                fm[v] = T(0.5) * Num<T>::fma_(-al(v, 2), u[v], F[v]);
             }
+        };
+        // the thread index, with resistivity not known to be the same from
+        // plane to plane: the indices formed from it are not kept (spills)
+        auto fresh = [&](int i) {
+            if constexpr (RESIST)
+                asm volatile("" : "+v"(i));
+            return i;
         };
         // F_D(u(p)) of the whole padded plane into sF
         auto plane_flux = [&](auto dc) {
             constexpr int D = decltype(dc)::value;
-            for (int c = t; c < XSM; c += NTM) {
+            for (int c = fresh(t); c < XSM; c += NTM) {
                 T u[NV], F[NV];
 #pragma unroll
                 for (int v = 0; v < NV; v++)
@@ -269,21 +299,20 @@ __global__ void __launch_bounds__(NTM) k_step_mmc3(StepArgs a)
             qz = eta * (jy * uc[BX] - jx * uc[BY]);
         };
 
-        // column registers: u of planes p-1 .. p+2, the z split fluxes
+        // column registers: u of planes p-1 .. p+1, the z split fluxes
         // fp_z(p-1), fp_z(p), fm_z(p), the carried g+ of the face p-3/2 and
         // f~-_z(p-1), the z flux of the face p-3/2, the in-plane result of
         // plane p-1 (finished with its z faces), eta J of planes p-1, p-2
-        T um[NV], u0[NV], up[NV], upp[NV];
+        T um[NV], u0[NV], up[NV];
         T fpz_m1[NV], fpz_0[NV], fmz_0[NV], gp_prev[NV], ftm_prev[NV], fz_prev[NV], Wc[NV];
         T jm1[3] = {T(0), T(0), T(0)}, jm2[3] = {T(0), T(0), T(0)};
-        load(um, -2);
-        load(u0, -1);
-        load(up, 0);
-        load(upp, 1);
+        load(um, z0 - 2);
+        load(u0, z0 - 1);
+        load(up, z0);
         {
             T tmp[NV];
-            split(std::integral_constant<int, 2>{}, um, fpz_m1, tmp);
-            split(std::integral_constant<int, 2>{}, u0, fpz_0, fmz_0);
+            split_z(um, fpz_m1, tmp);
+            split_z(u0, fpz_0, fmz_0);
         }
 #pragma unroll
         for (int v = 0; v < NV; v++) {
@@ -295,18 +324,18 @@ __global__ void __launch_bounds__(NTM) k_step_mmc3(StepArgs a)
         T xr[NV], xc[NV];
         if (isring) {
             T r0[NV];
-            load_x(r0, -1);
-            T *rb = rslot(-1);
+            load_x(r0, z0 - 1);
+            T *rb = rslot(z0 - 1);
 #pragma unroll
             for (int v = 0; v < NV; v++)
                 rb[v * NRM + ri] = r0[v];
-            load_x(xr, 0);
+            load_x(xr, z0);
         } else if (isout) {
-            load_x(xc, -1);
+            load_x(xc, z0 - 1);
         }
 
-        for (int p = -1; p <= NB; ++p) {
-            const bool kI = p >= 0 && p < NB;
+        for (int p = z0 - 1; p <= z1; ++p) {
+            const bool kI = p >= z0 && p < z1;
             // ---- (A) publish u(p); ring plane p+1; prefetch
 #pragma unroll
             for (int v = 0; v < NV; v++)
@@ -319,18 +348,18 @@ __global__ void __launch_bounds__(NTM) k_step_mmc3(StepArgs a)
                     su[v * XSM + xq] = rk[v * NRM + ri];
                     rn[v * NRM + ri] = xr[v];
                 }
-                if (p + 2 <= NB)
+                if (p + 2 <= z1)
                     load_x(xr, p + 2);
             } else if (isout) {
 #pragma unroll
                 for (int v = 0; v < NV; v++)
                     su[v * XSM + xq] = xc[v];
-                if (p + 1 <= NB)
+                if (p + 1 <= z1)
                     load_x(xc, p + 1);
             }
-            T un[NV];  // u(p+3), consumed two planes later
-            if (p + 3 <= NB + 1) {
-                load(un, p + 3);
+            T un[NV];  // u(p+2), the next plane's up
+            if (p + 2 <= z1 + 1) {
+                load(un, p + 2);
             } else {
 #pragma unroll
                 for (int v = 0; v < NV; v++)
@@ -346,7 +375,7 @@ __global__ void __launch_bounds__(NTM) k_step_mmc3(StepArgs a)
                 curl(q, u0, um, up, e, qz);
 #pragma unroll
                 for (int i = 0; i < 5; i++)
-                    sj[i * XSM + q] = e[i];
+                    sj[i * XE + ei(qx, qy)] = e[i];
                 jc[0] = e[0];
                 jc[1] = e[1];
                 jc[2] = qz;
@@ -363,7 +392,7 @@ __global__ void __launch_bounds__(NTM) k_step_mmc3(StepArgs a)
                     curl(xq, ur, urm, urp, er, qr);
 #pragma unroll
                     for (int i = 0; i < 5; i++)
-                        sj[i * XSM + xq] = er[i];
+                        sj[i * XE + xe] = er[i];
                 }
             }
             __syncthreads();
@@ -388,7 +417,7 @@ __global__ void __launch_bounds__(NTM) k_step_mmc3(StepArgs a)
 
             // ---- (E) y and z terms, u~(p); the z face p-1/2 finishes plane p-1
             T fpz_p1[NV], fmz_p1[NV];
-            split(std::integral_constant<int, 2>{}, up, fpz_p1, fmz_p1);
+            split_z(up, fpz_p1, fmz_p1);
             T ut[NV];
 #pragma unroll
             for (int v = 0; v < NV; v++) {
@@ -407,9 +436,9 @@ __global__ void __launch_bounds__(NTM) k_step_mmc3(StepArgs a)
                     urp[v] = rp[v * NRM + ri];
                 }
                 T fpa[NV], fma[NV], fpb[NV], fmb[NV], fpc[NV], fmc[NV];
-                split(std::integral_constant<int, 2>{}, urm, fpa, fma);
-                split(std::integral_constant<int, 2>{}, ur, fpb, fmb);
-                split(std::integral_constant<int, 2>{}, urp, fpc, fmc);
+                split_z(urm, fpa, fma);
+                split_z(ur, fpb, fmb);
+                split_z(urp, fpc, fmc);
 #pragma unroll
                 for (int v = 0; v < NV; v++) {
                     accr[v] += pred_term(v, xq, PD, 1);
@@ -419,12 +448,12 @@ __global__ void __launch_bounds__(NTM) k_step_mmc3(StepArgs a)
             }
             {
                 T ftp[NV], ftm[NV];
-                split(std::integral_constant<int, 2>{}, ut, ftp, ftm);
+                split_z(ut, ftp, ftm);
                 T fz[NV];
 #pragma unroll
                 for (int v = 0; v < NV; v++) {
                     const T gp_cur = ftp[v] - fpz_m1[v];
-                    if (p >= 0) {
+                    if (p >= z0) {
                         const T h = fpz_m1[v] + fmz_0[v];
                         const T gm_cur = fmz_0[v] - ftm_prev[v];
                         const T gm_nxt = fmz_p1[v] - ftm[v];
@@ -436,7 +465,7 @@ __global__ void __launch_bounds__(NTM) k_step_mmc3(StepArgs a)
                     gp_prev[v] = gp_cur;
                     ftm_prev[v] = ftm[v];
                 }
-                if (p >= 1) {
+                if (p > z0) {
                     T o[NV];
 #pragma unroll
                     for (int v = 0; v < NV; v++)
@@ -451,7 +480,7 @@ __global__ void __launch_bounds__(NTM) k_step_mmc3(StepArgs a)
                     for (int v = 0; v < NV; v++)
                         ob[v * P3 + (p - 1 + NG) * XSM + q] = o[v];
                 }
-                if (p == 0 || p == NB) {
+                if ((p == 0 && z0 == 0) || p == NB) {
                     const int fb = a.fbidx[(size_t)slot * 6 + 4 + (p == NB ? 1 : 0)];
                     if (fb >= 0) {
                         const int tt = qx + NB * qy;
@@ -475,7 +504,7 @@ __global__ void __launch_bounds__(NTM) k_step_mmc3(StepArgs a)
                 tilde_flux(std::integral_constant<int, 0>{});
                 plane_flux(std::integral_constant<int, 0>{});
                 __syncthreads();
-                for (int f = t; f < NFACE; f += NTM)
+                for (int f = fresh(t); f < NFACE; f += NTM)
                     face(std::integral_constant<int, 0>{}, f % (NB + 1) - 1, f / (NB + 1), p, f);
                 __syncthreads();
                 T div[NV];
@@ -489,7 +518,7 @@ __global__ void __launch_bounds__(NTM) k_step_mmc3(StepArgs a)
                 tilde_flux(std::integral_constant<int, 1>{});
                 plane_flux(std::integral_constant<int, 1>{});
                 __syncthreads();
-                for (int f = t; f < NFACE; f += NTM)
+                for (int f = fresh(t); f < NFACE; f += NTM)
                     face(std::integral_constant<int, 1>{}, f % NB, f / NB - 1, p, f);
                 __syncthreads();
 #pragma unroll
@@ -514,14 +543,15 @@ __global__ void __launch_bounds__(NTM) k_step_mmc3(StepArgs a)
                 }
                 // in-plane resistive terms -curl(eta J) and -div((eta J) x B)
                 if constexpr (RESIST) {
-                    const T *J0 = sj, *J1 = sj + XSM, *J2 = sj + 2 * XSM, *Q0 = sj + 3 * XSM,
-                            *Q1 = sj + 4 * XSM;
-                    Wc[BX] = Wc[BX] + dt * (-((J2[q + PD] - J2[q - PD]) * i2d[1]));
-                    Wc[BY] = Wc[BY] + dt * ((J2[q + 1] - J2[q - 1]) * i2d[0]);
-                    Wc[BZ] = Wc[BZ] + dt * ((J0[q + PD] - J0[q - PD]) * i2d[1] -
-                                            (J1[q + 1] - J1[q - 1]) * i2d[0]);
-                    Wc[EN] = Wc[EN] + dt * ((Q0[q + 1] - Q0[q - 1]) * i2d[0] +
-                                            (Q1[q + PD] - Q1[q - PD]) * i2d[1]);
+                    const int g = ei(qx, qy);
+                    const T *J0 = sj, *J1 = sj + XE, *J2 = sj + 2 * XE, *Q0 = sj + 3 * XE,
+                            *Q1 = sj + 4 * XE;
+                    Wc[BX] = Wc[BX] + dt * (-((J2[g + EW] - J2[g - EW]) * i2d[1]));
+                    Wc[BY] = Wc[BY] + dt * ((J2[g + 1] - J2[g - 1]) * i2d[0]);
+                    Wc[BZ] = Wc[BZ] + dt * ((J0[g + EW] - J0[g - EW]) * i2d[1] -
+                                            (J1[g + 1] - J1[g - 1]) * i2d[0]);
+                    Wc[EN] = Wc[EN] + dt * ((Q0[g + 1] - Q0[g - 1]) * i2d[0] +
+                                            (Q1[g + EW] - Q1[g - EW]) * i2d[1]);
                 }
             }
             __syncthreads();  // su, sF, sj reused by the next plane
@@ -531,8 +561,7 @@ __global__ void __launch_bounds__(NTM) k_step_mmc3(StepArgs a)
             for (int v = 0; v < NV; v++) {
                 um[v] = u0[v];
                 u0[v] = up[v];
-                up[v] = upp[v];
-                upp[v] = un[v];
+                up[v] = un[v];
             }
 #pragma unroll
             for (int i = 0; i < 3; i++) {
@@ -558,7 +587,8 @@ hipError_t launch_step_mmc3(bool fp64, bool resist, const StepArgs &a, int grid,
 {
     if (a.nitems <= 0)
         return hipSuccess;
-    const int g = grid > 0 ? (grid < a.nitems ? grid : a.nitems) : a.nitems;
+    const int items = marches_grid(a.nleaves, march_slots(a.ncu, fp64 ? 8 : 4), MAXSEG);
+    const int g = grid > 0 && grid < items ? grid : items;
     if (fp64) {
         if (resist)
             launch_mmc3_lim<double, false, true>(a, g, s);

@@ -21,6 +21,7 @@ struct Num<double> {
     static __device__ __forceinline__ double rcp(double x) { return rcp64(x); }
     static __device__ __forceinline__ double sqrt_(double x) { return sqrt64(x); }
     static __device__ __forceinline__ double div(double a, double b) { return div64(a, b); }
+    static __device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
     static __device__ __forceinline__ double max_(double a, double b) { return __builtin_fmax(a, b); }
     static __device__ __forceinline__ double min_(double a, double b) { return __builtin_fmin(a, b); }
     // b where the mask m is 0, a where it is all ones
@@ -37,6 +38,7 @@ struct Num<float> {
     static __device__ __forceinline__ float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
     static __device__ __forceinline__ float sqrt_(float x) { return __builtin_amdgcn_sqrtf(x); }
     static __device__ __forceinline__ float div(float a, float b) { return a * __builtin_amdgcn_rcpf(b); }
+    static __device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
     static __device__ __forceinline__ float max_(float a, float b) { return __builtin_fmaxf(a, b); }
     static __device__ __forceinline__ float pick(unsigned m, float a, float b)
     {
@@ -124,6 +126,43 @@ struct Phys {
         T vx = u[MX] * ir, vy = u[MY] * ir, vz = u[MZ] * ir;
         T me = T(0.5) * (u[BX] * u[BX] + u[BY] * u[BY] + u[BZ] * u[BZ]);
         return pressure(u, ir, vx, vy, vz, me) > T(0);
+    }
+
+    // flux<2, false> with the contractions written out, so that every inlined
+    // instance gives the same bits
+    __device__ __forceinline__ void flux_z(const T u[NV], T ch2, T f[NV]) const
+    {
+#pragma clang fp contract(off)
+        using N = Num<T>;
+        const T ir = N::rcp(u[RHO]);
+        const T v[3] = {u[MX] * ir, u[MY] * ir, u[MZ] * ir};
+        const T B[3] = {u[BX], u[BY], u[BZ]};
+        const T me = T(0.5) * N::fma_(B[2], B[2], N::fma_(B[1], B[1], B[0] * B[0]));
+        T pr;
+        if constexpr (MIXED) {
+            using D = Num<double>;
+            const double m[3] = {(double)u[MX], (double)u[MY], (double)u[MZ]};
+            const double b[3] = {(double)u[BX], (double)u[BY], (double)u[BZ]};
+            double r = (double)ir;
+            r = r * D::fma_(-(double)u[RHO], r, 2.0);  // one Newton step on 1/rho
+            const double m2 = D::fma_(m[2], m[2], D::fma_(m[1], m[1], m[0] * m[0]));
+            const double b2 = D::fma_(b[2], b[2], D::fma_(b[1], b[1], b[0] * b[0]));
+            pr = (T)(gm1d * D::fma_(-0.5, D::fma_(m2, r, b2), (double)u[EN]));
+        } else {
+            const T k2 = N::fma_(u[MZ], v[2], N::fma_(u[MY], v[1], u[MX] * v[0]));
+            pr = gm1 * (N::fma_(T(-0.5), k2, u[EN]) - me);
+        }
+        const T pt = pr + me;
+        const T vb = N::fma_(v[2], B[2], N::fma_(v[1], B[1], v[0] * B[0]));
+        f[RHO] = u[MZ];
+        f[MX] = N::fma_(u[MX], v[2], -(B[0] * B[2]));
+        f[MY] = N::fma_(u[MY], v[2], -(B[1] * B[2]));
+        f[MZ] = N::fma_(u[MZ], v[2], -(B[2] * B[2])) + pt;
+        f[BX] = N::fma_(B[0], v[2], -(B[2] * v[0]));
+        f[BY] = N::fma_(B[1], v[2], -(B[2] * v[1]));
+        f[BZ] = u[PSI];
+        f[EN] = N::fma_(u[EN] + pt, v[2], -(B[2] * vb));
+        f[PSI] = ch2 * B[2];
     }
 
     // EGLM flux along D (MHD-1..MHD-5); returns |v_D| + c_f,D if SPEED

@@ -25,4 +25,47 @@ __device__ __forceinline__ void xcd_range(int nitems, int &first, int &stride, i
     end = (int)hi;
 }
 
+// Blocks marched by one workgroup each, split so that the last round of an
+// XCD is not nearly empty: of the XCD's blocks (consecutive ones, as above)
+// those that fill whole rounds of its `slots` resident workgroups are whole
+// items, and the rest are cut into 2^lseg march segments each, the most that
+// are resident at once (and at most 2^lmax).
+struct Marches {
+    int lo, full, lseg, n;  // first block, whole blocks, segments of the others, items
+};
+
+__host__ __device__ inline Marches marches_of(int lo, int nblocks, int slots, int lmax)
+{
+    const int rest = nblocks % slots;
+    int l = 0;
+    while (rest > 0 && l < lmax && rest << (l + 1) <= slots)
+        l++;
+    return {lo, nblocks - rest, l, nblocks - rest + (rest << l)};
+}
+
+// this XCD's items; the calling workgroup takes first, first + stride, .. < n
+__device__ __forceinline__ Marches xcd_marches(int nblocks, int slots, int lmax, int &first, int &stride)
+{
+    int lo, hi;
+    xcd_range(nblocks, lo, stride, hi);
+    first = blockIdx.x >> 3;
+    return marches_of(lo - first, hi - (lo - first), slots, lmax);
+}
+
+// item j: its block, and its segment among 2^lseg
+__device__ __forceinline__ int march_item(const Marches &m, int j, int &seg, int &lseg)
+{
+    const int k = j - m.full;
+    seg = k < 0 ? 0 : k & ((1 << m.lseg) - 1);
+    lseg = k < 0 ? 0 : m.lseg;
+    return m.lo + (k < 0 ? j : m.full + (k >> m.lseg));
+}
+
+// workgroups for one item each
+inline int marches_grid(int nblocks, int slots, int lmax)
+{
+    const int a = marches_of(0, nblocks / 8, slots, lmax).n, b = marches_of(0, (nblocks + 7) / 8, slots, lmax).n;
+    return 8 * (a > b ? a : b);
+}
+
 }  // namespace mapk

@@ -146,3 +146,45 @@ def test_complete_frames_3d(copies, precision):
         out.append(s.U.clone())
     assert not out[0].isnan().any()
     assert torch.equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_segments_of_a_3d_march(precision):
+    """MacCormack with resistivity on one tree (15 leaves, each march in 8
+    segments of 2 planes) and on 20, 40 and 150 copies of it: 37 or 38 leaves
+    per XCD (32 whole, the others in 4 segments), 75 (11 in 2) and 281 (25
+    whole), the same state bit for bit; FP64 to round-off the oracle's."""
+    sd = W.SimDesc(lo=(0, 0, 0), hi=(1, 1, 1), nbase=(2, 2, 2),
+                   bc=(("periodic",) * 2, ("outflow",) * 2, ("periodic",) * 2))
+
+    def tree(copies):
+        keys = []
+        for s in range(copies):
+            base = W.base_keys(s, sd.nbase, 3)
+            keys += [base, W.children_of(base[3:4], 3)]
+        return W.Workload(name="marches", ndim=3, sims=[sd] * copies, keys=np.concatenate(keys), eta=1e-3,
+                          ic=lambda wl, sim, lv, x, y, z, g: [
+                              1 + 0.3 * np.sin(2 * np.pi * (x + z)), 0.4 * np.cos(2 * np.pi * y) + 0 * x,
+                              0.3 * np.sin(2 * np.pi * x), 0.2 * np.cos(2 * np.pi * z), 0.5 + 0 * x,
+                              0.4 + 0.1 * np.sin(2 * np.pi * y), 0.3 + 0 * x, 0.6 + 0 * x, 0 * x],
+                          scheme="mmc", precision=precision, glm_mode="fastspeed")
+
+    def run(copies):
+        s = Simulation(tree(copies), device="cuda:0")
+        s.load_initial()
+        s.advance(2)
+        s.sync()
+        return s.state_by_key()[:, :, 2:-2, 2:-2, 2:-2]
+
+    one = run(1)
+    assert np.isfinite(one).all()
+    if precision == "fp64":
+        A = orc.load_workload(tree(1))
+        A.run(2)
+        o = A.state[:, :, 2:-2, 2:-2, 2:-2]
+        for k in range(8):
+            assert np.abs(one[:, k] - o[:, k]).max() <= 1e-11 * np.abs(o[:, k]).max()
+    for copies in (20, 40, 150):
+        many = run(copies)
+        for s in (0, copies // 2, copies - 1):
+            assert np.array_equal(many[s * 16:(s + 1) * 16], one), f"{copies} copies, simulation {s}"
