@@ -289,14 +289,18 @@ map_status map_graph_run(map_ctx *ctx, void *U, map_dt *dt_dev, int nsteps, void
 /* MAP_LAUNCH_BATCHED: one launch per stage over the joint work list of all
  * levels and simulations (persistent workgroups); MAP_LAUNCH_PER_BLOCK: one
  * launch per block (the plain baseline).  grid_step / grid_fill: number of
- * workgroups of the batched step / fill launches (0 = one per work item). */
+ * workgroups of the batched step / fill launches (0 = one per work item, but
+ * as many as run at once for the 3-D FP32 LF and WENO and the 2-D MacCormack
+ * updates). */
 map_status map_set_launch(map_ctx *ctx, int mode, int grid_step, int grid_fill);
 
 /* Launch shapes of the batched stages (map_set_launch sets the first three). */
 typedef struct {
     int mode;            /* MAP_LAUNCH_BATCHED or MAP_LAUNCH_PER_BLOCK */
     int grid_step;       /* workgroups of the update launch; 0 = one per work
-                            item, > 0 = a persistent grid striding over them */
+                            item (3-D FP32 LF and WENO, 2-D MacCormack: as many
+                            as run at once), > 0 = a persistent grid striding
+                            over them */
     int grid_fill;       /* the same for the parent-frame copies of the fill */
     int step_shape;      /* workgroup shape of the update: 2-D LF and WENO,
                             0 = 14 blocks in 4 waves, 1 = 7 blocks in 2 waves;

@@ -479,7 +479,7 @@ __global__ void __launch_bounds__(nt_restrict(NDIM, PC)) k_restrict(RestrictArgs
     using V = typename Pair<T>::V;
     constexpr int P = FG<NDIM>::P, NI = FG<NDIM>::NI;
     constexpr int K0 = VarRange<EO>::K0, K1 = VarRange<EO>::K1;
-    constexpr int NCH = NDIM == 3 ? 8 : 4, NC = NDIM == 3 ? 8 : 4;
+    constexpr int NCH = NDIM == 3 ? 8 : 4;
     constexpr int H = NB / 2;
     static_assert(!CFL || (!EO && NTA == NB * NB), "CFL: all variables, one column per thread");
     __shared__ unsigned long long smax[CFL ? NCH : 1];
@@ -488,61 +488,70 @@ __global__ void __launch_bounds__(nt_restrict(NDIM, PC)) k_restrict(RestrictArgs
     if (EO && sub_idle(a.dt, a.nsims, a.sub))
         return;
     // parent cell d of ub from the 2^d cells of child tile cu at c0 (its
-    // lowest corner), keeping those cells' values in cv for the CFL speeds
-    auto restrict_cell = [&](T *ub, const T *cu, int c0, int d, T (&cv)[CFL ? NV : 1][CFL ? NC : 1]) {
+    // lowest corner); with `leafc` the CFL speeds of those cells into the
+    // running maximum mh.  In 3-D with CFL the two z layers of four cells are
+    // taken one after the other: eight cells' values at once left three (FP32)
+    // or two (FP64) waves per SIMD (140 and 194 registers; 106 and 152 now),
+    // too few to load while others form speeds: two cycles of 1464 FP32 leaves
+    // 1228 -> 1201 us, of 19264 28.9 -> 28.65 ms.  Fewer registers by launch
+    // bounds (96 and 128) spill and are no faster
+    auto restrict_cell = [&](T *ub, const T *cu, int c0, int d, bool leafc, double &mh, unsigned &bad,
+                             unsigned &nonfin) {
+        constexpr int NL = NDIM == 3 ? 2 : 1;
+        T sum[K1];
+        auto layer = [&](int h) {
+            T cv[CFL ? NV : 1][4];
 #pragma unroll
-        for (int k = K0; k < K1; k++) {
-            const T *q = cu + (size_t)k * P + c0;
-            const V r0 = *reinterpret_cast<const V *>(q);
-            const V r1 = *reinterpret_cast<const V *>(q + PD);
-            T v;
-            if constexpr (NDIM == 2) {
-                v = ((r0.x + r0.y) + (r1.x + r1.y)) * T(0.25);
-            } else {
-                const V r2 = *reinterpret_cast<const V *>(q + PD * PD);
-                const V r3 = *reinterpret_cast<const V *>(q + PD * PD + PD);
-                v = (((r0.x + r0.y) + (r1.x + r1.y)) + ((r2.x + r2.y) + (r3.x + r3.y))) * T(0.125);
+            for (int k = K0; k < K1; k++) {
+                const T *q = cu + (size_t)k * P + c0 + h * (PD * PD);
+                const V r0 = *reinterpret_cast<const V *>(q);
+                const V r1 = *reinterpret_cast<const V *>(q + PD);
+                const T v = (r0.x + r0.y) + (r1.x + r1.y);
+                sum[k] = h == 0 ? v : sum[k] + v;
                 if constexpr (CFL) {
-                    cv[k][4] = r2.x;
-                    cv[k][5] = r2.y;
-                    cv[k][6] = r3.x;
-                    cv[k][7] = r3.y;
+                    cv[k][0] = r0.x;
+                    cv[k][1] = r0.y;
+                    cv[k][2] = r1.x;
+                    cv[k][3] = r1.y;
                 }
             }
             if constexpr (CFL) {
-                cv[k][0] = r0.x;
-                cv[k][1] = r0.y;
-                cv[k][2] = r1.x;
-                cv[k][3] = r1.y;
-            }
-            ub[(size_t)k * P + d] = v;
-        }
-    };
-    // the CFL speeds of those child cells into the running maximum mh
-    auto cell_speeds = [&](const T (&cv)[CFL ? NV : 1][CFL ? NC : 1], double &mh, unsigned &bad,
-                           unsigned &nonfin) {
-        if constexpr (CFL) {
+                if (!leafc)
+                    return;
 #pragma unroll
-            for (int c = 0; c < NC; c++) {
-                double u[NV];
-                bool fin = true;
+                for (int c = 0; c < 4; c++) {
+                    double u[NV];
+                    bool fin = true;
 #pragma unroll
-                for (int k = 0; k < NV; k++) {
-                    u[k] = (double)cv[k][c];
-                    fin = fin && isfinite(u[k]);
+                    for (int k = 0; k < NV; k++) {
+                        u[k] = (double)cv[k][c];
+                        fin = fin && isfinite(u[k]);
+                    }
+                    if (!fin) {
+                        nonfin++;
+                        continue;
+                    }
+                    double pr;
+                    bool b;
+                    const double sp = cfl_speed<NDIM>(u, a.gamma, pr, b);
+                    if (b)
+                        bad++;
+                    mh = sp > mh ? sp : mh;
                 }
-                if (!fin) {
-                    nonfin++;
-                    continue;
-                }
-                double pr;
-                bool b;
-                const double sp = cfl_speed<NDIM>(u, a.gamma, pr, b);
-                if (b)
-                    bad++;
-                mh = sp > mh ? sp : mh;
             }
+        };
+        if constexpr (CFL && NL == 2) {
+#pragma unroll 1
+            for (int h = 0; h < NL; h++)
+                layer(h);
+        } else {
+#pragma unroll
+            for (int h = 0; h < NL; h++)
+                layer(h);
         }
+#pragma unroll
+        for (int k = K0; k < K1; k++)
+            ub[(size_t)k * P + d] = sum[k] * T(NDIM == 3 ? 0.125 : 0.25);
     };
     auto count = [&](unsigned bad, unsigned nonfin) {
         if (bad)
@@ -568,11 +577,8 @@ __global__ void __launch_bounds__(nt_restrict(NDIM, PC)) k_restrict(RestrictArgs
             {
                 const int i = threadIdx.x, x = i % H, y = (i / H) % H,
                           z = NDIM == 3 ? i / (H * H) : 0;
-                T cv[CFL ? NV : 1][CFL ? NC : 1];
                 restrict_cell(ub, cu, lin<NDIM>(2 * x, 2 * y, 2 * z), lin<NDIM>(ox + x, oy + y, oz + z),
-                              cv);
-                if (leafc)
-                    cell_speeds(cv, m, bad, nonfin);
+                              leafc, m, bad, nonfin);
             }
             if constexpr (CFL) {
                 count(bad, nonfin);
@@ -614,10 +620,8 @@ __global__ void __launch_bounds__(nt_restrict(NDIM, PC)) k_restrict(RestrictArgs
                 const int child = a.children[(size_t)slot * 8 + cbit];
                 const T *cu = U + (size_t)child * NV * P;
                 const int lx = fx % NB, ly = fy % NB, lz = NDIM == 3 ? fz % NB : 0;
-                T cv[CFL ? NV : 1][CFL ? NC : 1];
-                restrict_cell(ub, cu, lin<NDIM>(lx, ly, lz), lin<NDIM>(X, Y, Z), cv);
-                if (CFL && a.leaf_of[child] >= 0)
-                    cell_speeds(cv, m[NDIM == 3 ? fz / NB : 0], bad, nonfin);
+                restrict_cell(ub, cu, lin<NDIM>(lx, ly, lz), lin<NDIM>(X, Y, Z),
+                              CFL && a.leaf_of[child] >= 0, m[NDIM == 3 ? fz / NB : 0], bad, nonfin);
             }
             if constexpr (CFL) {
                 // this thread's children: the one of its column below the middle

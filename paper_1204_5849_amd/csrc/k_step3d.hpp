@@ -27,7 +27,7 @@
 // registers.
 //
 // What bounds it: issue on the three SIMDs that hold a ring wave, and the
-// waits at the barriers (waves wait 0.47 of their time; LDS bank conflicts, 5
+// waits at the barriers (waves wait 0.47 of their time; LDS bank conflicts, 8
 // times more with a wave on four adjacent rows, cost 0.04).  Against one thread per column for all
 // dimensions (two 4-wave workgroups per CU, 256 registers, 44 to 180 bytes of
 // them in scratch), per map_step on the Harris sheet with 4768 leaves: LF 1453
