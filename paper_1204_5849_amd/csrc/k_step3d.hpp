@@ -150,7 +150,6 @@ struct March3d {
         const BlockRec br = a.blk[slot];
         const map_dt rec = a.dt[br.sim];
         const double *dxp = a.lvl_dx + ((size_t)br.sim * (MAXL + 1) + br.level) * 3;
-        const T hdt = uni((T)(0.5 * (rec.dt / dxp[D])));
         const T dt = uni((T)rec.dt), ch = uni((T)rec.ch), ch2 = uni((T)(rec.ch * rec.ch));
         const T rx = uni((T)(rec.dt / dxp[0])), ry = uni((T)(rec.dt / dxp[1])),
                 rz = uni((T)(rec.dt / dxp[2]));
@@ -253,7 +252,7 @@ struct March3d {
             T uc[NV], dl[NV], acc[NV];
             T L[NV], R[NV];
             bool ok = true;
-            T src[3] = {T(0), T(0), T(0)};  // EGLM source terms x dt: m (x threads), e (y)
+            T src[3] = {T(0), T(0), T(0)};  // EGLM source terms: m (x threads), e (y)
             T jc[3] = {T(0), T(0), T(0)};
             if (on) {
                 const T *const pa = D == 2 ? sm + q : sc + q - ST, *const pb = D == 2 ? sn + q : sc + q + ST;
@@ -285,18 +284,14 @@ struct March3d {
                     flux_w<D>(s1, w, ch2, f2);
 #pragma unroll
                     for (int v = 0; v < NV; v++) {
-                        // (rho, psi and B_d have linear fluxes)
-                        const T df = v == RHO ? dl[MX + D]
-                                              : (v == PSI ? ch2 * dl[BX + D]
-                                                          : (v == BX + D ? dl[PSI] : f1[v] - f2[v]));
-                        acc[v] = hdt * df;
+                        acc[v] = f1[v] - f2[v];
                         sh.sac[D][v * NCELLD + cell] = acc[v];
                     }
                     sh.sok[D][cell] = ok;
                 } else if (D == 2 ? !RING : (kI && rface)) {
 #pragma unroll
                     for (int v = 0; v < NV; v++)
-                        weno_pair(a_[v], uc[v], b_[v], L[v], R[v]);
+                        weno_pair<true>(a_[v], uc[v], b_[v], L[v], R[v]);
                 }
                 // EGLM sources from central differences of u^n
                 if (FIN && kI && a.eglm) {
@@ -307,13 +302,13 @@ struct March3d {
                         divb += (sn[BZ * XSD + q] - sm[BZ * XSD + q]) * iz;
 #pragma unroll
                         for (int i = 0; i < 3; i++)
-                            src[i] = dt * (divb * uc[BX + i]);
+                            src[i] = divb * uc[BX + i];
                     } else {
                         const T *ps = sc + PSI * XSD + q;
                         T bgp = uc[BX] * ((ps[1] - ps[-1]) * ix);
                         bgp += uc[BY] * ((ps[PD] - ps[-PD]) * iy);
                         bgp += uc[BZ] * ((sn[PSI * XSD + q] - sm[PSI * XSD + q]) * iz);
-                        src[0] = dt * bgp;
+                        src[0] = bgp;
                     }
                 }
                 // eta J and eta (J x B), by the y waves
@@ -351,7 +346,8 @@ struct March3d {
                         const T x = D == 0 ? acc[v] : sh.sac[0][v * NCELLD + cell];
                         const T y = D == 1 ? acc[v] : sh.sac[1][v * NCELLD + cell];
                         const T z = D == 2 ? acc[v] : sh.sac[2][v * NCELLD + cell];
-                        ut[v] = uc[v] - ((x + y) + z);
+                        ut[v] = uc[v] - Num<T>::fma_(T(0.5) * rz, z,
+                                                     Num<T>::fma_(T(0.5) * ry, y, T(0.5) * rx * x));
                     }
                     if (!okc) {
 #pragma unroll
@@ -474,11 +470,11 @@ struct March3d {
                         *Q1 = J0 + 4 * XSD;
                 if (kI) {
                     if constexpr (D == 0) {
-                        rin[0] = -(dt * ((J2[PD] - J2[-PD]) * iy));
+                        rin[0] = -((J2[PD] - J2[-PD]) * iy);
                     } else {
-                        rin[0] = dt * ((J2[1] - J2[-1]) * ix);
-                        rin[1] = dt * ((J0[PD] - J0[-PD]) * iy - (J1[1] - J1[-1]) * ix);
-                        rin[2] = dt * ((Q0[1] - Q0[-1]) * ix + (Q1[PD] - Q1[-PD]) * iy);
+                        rin[0] = (J2[1] - J2[-1]) * ix;
+                        rin[1] = (J0[PD] - J0[-PD]) * iy - (J1[1] - J1[-1]) * ix;
+                        rin[2] = (Q0[1] - Q0[-1]) * ix + (Q1[PD] - Q1[-PD]) * iy;
                     }
                 }
                 if constexpr (D == 0)
@@ -526,14 +522,18 @@ struct March3d {
                             fzp[v] = fz[v];
                         }
                         if constexpr (D == 0) {
-                            Wc[MX] = Wc[MX] - src[0];
-                            Wc[MY] = Wc[MY] - src[1];
-                            Wc[MZ] = Wc[MZ] - src[2];
-                            Wc[BX] = Wc[BX] + rin[0];
+                            Wc[MX] = Wc[MX] - dt * src[0];
+                            Wc[MY] = Wc[MY] - dt * src[1];
+                            Wc[MZ] = Wc[MZ] - dt * src[2];
+                            if constexpr (RESIST)
+                                Wc[BX] = Wc[BX] + dt * rin[0];
                         } else {
-                            Wc[EN] = Wc[EN] - src[0] + rin[2];
-                            Wc[BY] = Wc[BY] + rin[0];
-                            Wc[BZ] = Wc[BZ] + rin[1];
+                            Wc[EN] = Wc[EN] - dt * src[0];
+                            if constexpr (RESIST) {
+                                Wc[BY] = Wc[BY] + dt * rin[0];
+                                Wc[BZ] = Wc[BZ] + dt * rin[1];
+                                Wc[EN] = Wc[EN] + dt * rin[2];
+                            }
                         }
                     }
                 }
