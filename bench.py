@@ -518,7 +518,7 @@ def launch_label(cfg, eager):
     how = "eager" if eager else "hipGraph"
     if cfg is None or cfg.get("mode", 0) != 0:
         return f"{how}, one launch per block"
-    kind = "persistent" if cfg.get("grid_step", 0) > 0 else "one workgroup per work item"
+    kind = "persistent" if cfg.get("grid_step", 0) > 0 else "default grid"
     return f"{how}, batched ({kind})"
 
 
