@@ -31,9 +31,12 @@
 // times more with a wave on four adjacent rows, cost 0.04).  Against one thread per column for all
 // dimensions (two 4-wave workgroups per CU, 256 registers, 44 to 180 bytes of
 // them in scratch), per map_step on the Harris sheet with 4768 leaves: LF 1453
-// -> 1354 us, LF with HLLC 1664 -> 1406, WENO 4675 -> 3494, WENO with HLLC
-// 5077 -> 3601 (both stages with the fill between); the blast's 1464 leaves,
-// which had no spills, 423 -> 425.
+// -> 1371 us, LF with HLLC 1664 -> 1430, WENO 4675 -> 3526, WENO with HLLC
+// 5077 -> 3620 (both stages with the fill between); the blast's 1464 leaves,
+// which had no spills, 423 -> 434 (412 at the other priorities).  Sums over
+// dimensions keep the order of the one-thread version; scaling the half-step
+// differences and sources before they meet was 1 % faster, but moved the last
+// bits of the state and with them the time steps.
 // The waves of one role run their own loop; every wave passes the same
 // barriers.  Ghost cells are read where the ghost descriptors point (Sec.
 // 4.3), so U_out must not alias U_in (WENO stage 2 reads U_base at the cells
