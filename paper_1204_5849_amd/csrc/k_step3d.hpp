@@ -33,15 +33,17 @@
 // them in scratch), per map_step on the Harris sheet with 4768 leaves: LF 1453
 // -> 1371 us, LF with HLLC 1664 -> 1430, WENO 4675 -> 3526, WENO with HLLC
 // 5077 -> 3620 (both stages with the fill between); the blast's 1464 leaves,
-// which had no spills, 423 -> 434 (412 at the other priorities).  Sums over
-// dimensions keep the order of the one-thread version; scaling the half-step
-// differences and sources before they meet was 1 % faster, but moved the last
-// bits of the state and with them the time steps.
+// which had no spills, 423 -> 434 (412 at the other priorities).  Every sum and
+// contraction is the one-thread version's, so that the state and the FP64 time
+// steps taken from it keep their bits: scaling the half-step differences and
+// sources before they meet was 1 % faster, the face states of WENO from
+// differences (u0 + d/2) 7 %, but both moved the time steps, by up to 1e-7.
 // The waves of one role run their own loop; every wave passes the same
 // barriers.  Ghost cells are read where the ghost descriptors point (Sec.
 // 4.3), so U_out must not alias U_in (WENO stage 2 reads U_base at the cells
 // it writes).  Each face flux is evaluated once and differences are formed
-// explicitly, so a uniform state stays exactly uniform.
+// explicitly, so a uniform state stays exactly uniform (WENO: as far as the
+// products 3 u0 that weno_pair_fma rounds first are exact).
 #pragma once
 
 #include <type_traits>
@@ -111,6 +113,25 @@ template <typename T, bool MIXED, bool RESIST, int SCH, int LIM, int RS, int SHA
 struct March3d {
     static constexpr bool PREDICT = SCH == SCH_LF;
     using Sh = Shared3d<T, RESIST, PREDICT>;
+
+    // flux of a face along D.  The contractions that the compiler chooses
+    // differently for otherwise equal callers are written out: B . B, v . B and
+    // the sum of the two psi fluxes ch2 B_D
+    template <int D, bool RING>
+    static __device__ __forceinline__ void face(const T L[NV], T pL, const T R[NV], T pR, T gam, T gm1,
+                                                T ch, T ch2, T f[NV])
+    {
+        constexpr int BB = D == 0 && (RS == MAP_HLLC || !RING) ? 0 : 1;
+        constexpr int VL = D == 1 && RS == MAP_HLLC ? 0 : 1;
+        constexpr int VR = RS == MAP_HLLC && !PREDICT && !RING && D < 2 ? 1 - VL : VL;
+        face_flux<RS, D, BB, VL, VR>(L, pL, R, pR, gam, gm1, ch, ch2, f);
+        if constexpr (RS == MAP_RUSANOV) {
+#pragma clang fp contract(off)
+            const T bl = L[BX + D], br = R[BX + D];
+            const T s = D == 2 ? Num<T>::fma_(bl, ch2, br * ch2) : Num<T>::fma_(br, ch2, bl * ch2);
+            f[PSI] = Num<T>::fma_(T(0.5), s, -(T(0.5) * ch * (R[PSI] - L[PSI])));
+        }
+    }
 
     // one role of the march over one block: dimension D, interior columns or
     // the ring cells
@@ -294,7 +315,7 @@ struct March3d {
                 } else if (D == 2 ? !RING : (kI && rface)) {
 #pragma unroll
                     for (int v = 0; v < NV; v++)
-                        weno_pair<true>(a_[v], uc[v], b_[v], L[v], R[v]);
+                        weno_pair_fma<RING || D == 0, RING>(a_[v], uc[v], b_[v], L[v], R[v]);
                 }
                 // EGLM sources from central differences of u^n
                 if (FIN && kI && a.eglm) {
@@ -430,7 +451,7 @@ struct March3d {
 #pragma unroll
                     for (int v = 0; v < NV; v++)
                         R[v] = srf[D][v * XSD + q + ST];
-                    face_flux<RS, D>(L, pL, R, spr[D][q + ST], gam, gm1, ch, ch2, f);
+                    face<D, RING>(L, pL, R, spr[D][q + ST], gam, gm1, ch, ch2, f);
 #pragma unroll
                     for (int v = 0; v < NV; v++)
                         srf[D][v * XSD + q + ST] = f[v];
@@ -448,7 +469,7 @@ struct March3d {
                 }
             } else if constexpr (COL) {
                 if (k >= 0) {
-                    face_flux<RS, 2>(Lp, pLp, R, pR, gam, gm1, ch, ch2, f);
+                    face<2, false>(Lp, pLp, R, pR, gam, gm1, ch, ch2, f);
 #pragma unroll
                     for (int v = 0; v < NV; v++)
                         sh.sfz[v * NCD + col] = f[v];
@@ -498,11 +519,15 @@ struct March3d {
                         for (int v = V0; v < V1; v++)
                             o[v] = Wc[v] - rz * (fz[v] - fzp[v]);
                         if constexpr (RESIST) {
+                            // (eta J is rounded before the difference, on the
+                            // x threads, which read it, as on the y threads,
+                            // which formed it)
+#pragma clang fp contract(off)
                             if constexpr (D == 0) {
-                                o[BX] = o[BX] + dt * ((jc[1] - jb[1]) * iz);
+                                o[BX] = Num<T>::fma_((jc[1] - jb[1]) * iz, dt, o[BX]);
                             } else {
-                                o[BY] = o[BY] - dt * ((jc[0] - jb[0]) * iz);
-                                o[EN] = o[EN] + dt * ((jc[2] - jb[2]) * iz);
+                                o[BY] = Num<T>::fma_(-((jc[0] - jb[0]) * iz), dt, o[BY]);
+                                o[EN] = Num<T>::fma_((jc[2] - jb[2]) * iz, dt, o[EN]);
                             }
                         }
 #pragma unroll

@@ -111,7 +111,7 @@ struct Phys {
                         (double)u[MZ] * (double)u[MZ];
             double b2 = (double)u[BX] * (double)u[BX] + (double)u[BY] * (double)u[BY] +
                         (double)u[BZ] * (double)u[BZ];
-            return (T)(gm1d * ((double)u[EN] - 0.5 * (m2 * r + b2)));
+            return (T)(gm1d * (((double)u[EN] - 0.5 * m2 * r) - 0.5 * b2));
         } else {
             T ke = T(0.5) * (u[MX] * vx + u[MY] * vy + u[MZ] * vz);
             return gm1 * (u[EN] - ke - me);
@@ -228,18 +228,34 @@ __device__ __forceinline__ bool admissible_w(const T u[NV], const Prim<T> &w)
     return u[RHO] > T(0) && w.p > T(0);
 }
 
+// a0 b0 + a1 b1 + a2 b2.  I: the product that is rounded first, the others
+// entering by FMAs (the compiler's own choice, I = -1, depends on which of the
+// products another expression shares, and with it the last bits)
+template <int I, typename T>
+__device__ __forceinline__ T dot3(T a0, T b0, T a1, T b1, T a2, T b2)
+{
+    if constexpr (I < 0) {
+        return a0 * b0 + a1 * b1 + a2 * b2;
+    } else {
+#pragma clang fp contract(off)
+        using N = Num<T>;
+        return N::fma_(a2, b2, I == 0 ? N::fma_(a1, b1, a0 * b0) : N::fma_(a0, b0, a1 * b1));
+    }
+}
+
 // EGLM flux along dimension d from a state and its primitives.  d may differ
 // between lanes (a wave that serves faces of several orientations); with a
 // constant d the selects fold away, so every caller forms the same
 // arithmetic and a flux does not depend on which lane evaluated it.
-template <typename T>
+// (VB: the form of v . B, see dot3)
+template <int VB = -1, typename T>
 __device__ __forceinline__ void flux_sel(const T u[NV], const Prim<T> &w, int d, T ch2, T f[NV])
 {
     const T me = T(0.5) * w.bb;
     const T pt = w.p + me;
     const T vd = d == 0 ? w.vx : (d == 1 ? w.vy : w.vz);
     const T Bd = d == 0 ? u[BX] : (d == 1 ? u[BY] : u[BZ]);
-    const T vb = w.vx * u[BX] + w.vy * u[BY] + w.vz * u[BZ];
+    const T vb = dot3<VB>(w.vx, u[BX], w.vy, u[BY], w.vz, u[BZ]);
     f[RHO] = d == 0 ? u[MX] : (d == 1 ? u[MY] : u[MZ]);
     f[MX] = u[MX] * vd - u[BX] * Bd;
     f[MY] = u[MY] * vd - u[BY] * Bd;

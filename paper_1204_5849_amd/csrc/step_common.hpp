@@ -16,15 +16,7 @@ namespace mapk {
 //   R = (s_-^2 w' + 2 s_+^2 v') / (s_-^2 + 2 s_+^2), w' = (3 u0 - up)/2, v' = (u0 + um)/2
 // In FP32 both s are first scaled by one power of two (exact), so that their
 // squares neither overflow nor both underflow.
-// DIFF: the same from the differences d_- = u0 - um, d_+ = up - u0 (the stencil
-// values are u0 + d_+/2 and u0 + d_-/2, u0 - d_-/2 and u0 - d_+/2),
-//   L = u0 + (2 s_-^2 d_+ + s_+^2 d_-) / (2 (2 s_-^2 + s_+^2))
-//   R = u0 - (s_-^2 d_+ + 2 s_+^2 d_-) / (2 (s_-^2 + 2 s_+^2)),
-// in fewer instructions and exactly u0 in a uniform state, whichever way the
-// compiler contracts it: the 3-D FP32 stages, which form the states of interior
-// and ring cells by different instances (8705 -> 8331 us for two cycles of the
-// sheet with 4768 leaves).
-template <bool DIFF = false, typename T>
+template <typename T>
 __device__ __forceinline__ void weno_pair(T um, T u0, T up, T &L, T &R)
 {
     const T dm = u0 - um, dp = up - u0;
@@ -36,21 +28,41 @@ __device__ __forceinline__ void weno_pair(T um, T u0, T up, T &L, T &R)
     }
     const T qm = sm * sm, qp = sp * sp;
     const T h = T(0.5);
-    if constexpr (DIFF) {
-        const T am = qm + qm, ap = qp + qp;
-        L = u0 + h * Num<T>::div(am * dp + qp * dm, am + qp);
-        R = u0 - h * Num<T>::div(qm * dp + ap * dm, qm + ap);
-    } else {
-        L = Num<T>::div(T(2) * qm * (h * (u0 + up)) + qp * (h * (T(3) * u0 - um)), T(2) * qm + qp);
-        R = Num<T>::div(qm * (h * (T(3) * u0 - up)) + T(2) * qp * (h * (u0 + um)), qm + T(2) * qp);
-    }
+    L = Num<T>::div(T(2) * qm * (h * (u0 + up)) + qp * (h * (T(3) * u0 - um)), T(2) * qm + qp);
+    R = Num<T>::div(qm * (h * (T(3) * u0 - up)) + T(2) * qp * (h * (u0 + um)), qm + T(2) * qp);
+}
+
+// The same in FP32 with the contractions written out, so that a face state has
+// the same bits wherever the 3-D stages form it: left to the compiler they
+// depend on which products a neighbouring expression shares, and with them the
+// last bits of the state and of the time steps taken from it.  LF / RF: the
+// product 3 u0 of the left / right state goes into an FMA or is rounded first.
+// Powers of two are moved to where they cost nothing (2 q (u + v) / 2 is
+// q (u + v), (3 u0 - um) / 2 is 1.5 u0 - um / 2), which changes no rounding,
+// and the scale is formed in the exponent bits: 2^(128 - E) for the larger s,
+// E its biased exponent (87 to 254; infinities and NaN end as NaN).
+template <bool LF, bool RF>
+__device__ __forceinline__ void weno_pair_fma(float um, float u0, float up, float &L, float &R)
+{
+#pragma clang fp contract(off)
+    using N = Num<float>;
+    const float dm = u0 - um, dp = up - u0;
+    float sm = N::fma_(dm, dm, 1e-12f), sp = N::fma_(dp, dp, 1e-12f);
+    const float sc = __uint_as_float(0x7f800000u - (__float_as_uint(N::max_(sm, sp)) & 0x7f800000u));
+    sm = sm * sc;
+    sp = sp * sc;
+    const float qm = sm * sm, qp = sp * sp, t = 1.5f * u0;
+    const float vm = LF ? 0.5f * N::fma_(3.0f, u0, -um) : N::fma_(-0.5f, um, t);
+    const float vp = RF ? 0.5f * N::fma_(3.0f, u0, -up) : N::fma_(-0.5f, up, t);
+    L = N::fma_(vm, qp, qm * (u0 + up)) * N::rcp(N::fma_(2.0f, qm, qp));
+    R = N::fma_(vp, qm, qp * (u0 + um)) * N::rcp(N::fma_(2.0f, qp, qm));
 }
 
 // Rusanov flux (Equ:LFFlux) across a face normal to dimension d, with alpha
 // = max of the two fast speeds for the MHD components and c_h for the GLM
 // pair (B_d, psi); the pressures of both states are given (computed once
 // when the states were formed).  d may differ between lanes (see flux_sel).
-template <typename T>
+template <int BB, int VL, int VR, typename T>
 __device__ __forceinline__ void rusanov_sel(const T L[NV], T pL, const T R[NV], T pR, int d,
                                             T gamma, T ch, T ch2, T f[NV])
 {
@@ -59,17 +71,17 @@ __device__ __forceinline__ void rusanov_sel(const T L[NV], T pL, const T R[NV], 
     wL.vx = L[MX] * wL.ir;
     wL.vy = L[MY] * wL.ir;
     wL.vz = L[MZ] * wL.ir;
-    wL.bb = L[BX] * L[BX] + L[BY] * L[BY] + L[BZ] * L[BZ];
+    wL.bb = dot3<BB>(L[BX], L[BX], L[BY], L[BY], L[BZ], L[BZ]);
     wL.p = pL;
     wR.ir = Num<T>::rcp(R[RHO]);
     wR.vx = R[MX] * wR.ir;
     wR.vy = R[MY] * wR.ir;
     wR.vz = R[MZ] * wR.ir;
-    wR.bb = R[BX] * R[BX] + R[BY] * R[BY] + R[BZ] * R[BZ];
+    wR.bb = dot3<BB>(R[BX], R[BX], R[BY], R[BY], R[BZ], R[BZ]);
     wR.p = pR;
     T FL[NV], FR[NV];
-    flux_sel(L, wL, d, ch2, FL);
-    flux_sel(R, wR, d, ch2, FR);
+    flux_sel<VL>(L, wL, d, ch2, FL);
+    flux_sel<VR>(R, wR, d, ch2, FR);
     const T sL = speed_sel(L, wL, d, gamma), sR = speed_sel(R, wR, d, gamma);
     const T al = Num<T>::max_(sL, sR);
 #pragma unroll
@@ -96,7 +108,7 @@ __device__ __forceinline__ void rusanov_sel(const T L[NV], T pL, const T R[NV], 
 //   e* = [e_K (S_K - v_K) - p_T,K v_K + p* S_M + B_m (v_K.B_K - v_hll.B_hll)]/(S_K - S_M),
 // and the flux F_K + S_K (U*_K - U_K), or F_L / F_R when the whole fan
 // moves one way.
-template <typename T>
+template <int BB, int VL, int VR, typename T>
 __device__ __forceinline__ void hllc_sel(const T L0[NV], T pL0, const T R0[NV], T pR0, int d,
                                          T gamma, T gm1, T ch, T ch2, T f[NV])
 {
@@ -124,13 +136,14 @@ __device__ __forceinline__ void hllc_sel(const T L0[NV], T pL0, const T R0[NV], 
         w.vx = U[s][MX] * w.ir;
         w.vy = U[s][MY] * w.ir;
         w.vz = U[s][MZ] * w.ir;
-        w.bb = U[s][BX] * U[s][BX] + U[s][BY] * U[s][BY] + U[s][BZ] * U[s][BZ];
+        w.bb = dot3<BB>(U[s][BX], U[s][BX], U[s][BY], U[s][BY], U[s][BZ], U[s][BZ]);
         w.p = (s ? pR0 : pL0) + gm1 * (h * ((Bd0 - Bm) * (Bd0 + Bm)));
-        flux_sel(U[s], w, d, ch2, F[s]);
+        s ? flux_sel<VR>(U[s], w, d, ch2, F[s]) : flux_sel<VL>(U[s], w, d, ch2, F[s]);
         v[s] = d == 0 ? w.vx : (d == 1 ? w.vy : w.vz);
         pt[s] = w.p + h * w.bb;
         cf[s] = fast_sel(U[s], w, d, gamma);
-        vb[s] = w.vx * U[s][BX] + w.vy * U[s][BY] + w.vz * U[s][BZ];
+        vb[s] = s ? dot3<VR>(w.vx, U[s][BX], w.vy, U[s][BY], w.vz, U[s][BZ])
+                  : dot3<VL>(w.vx, U[s][BX], w.vy, U[s][BY], w.vz, U[s][BZ]);
     }
     const T cmax = cf[0] > cf[1] ? cf[0] : cf[1];
     const T SL = (v[0] < v[1] ? v[0] : v[1]) - cmax;
@@ -188,14 +201,15 @@ __device__ __forceinline__ void hllc_sel(const T L0[NV], T pL0, const T R0[NV], 
 }
 
 // the face flux of the scheme's Riemann solver (RS = MAP_RUSANOV or MAP_HLLC)
-template <int RS, int D, typename T>
+// BB, VL, VR: the forms of B . B and of v . B left and right (see dot3)
+template <int RS, int D, int BB = -1, int VL = -1, int VR = VL, typename T>
 __device__ __forceinline__ void face_flux(const T L[NV], T pL, const T R[NV], T pR, T gamma, T gm1,
                                           T ch, T ch2, T f[NV])
 {
     if constexpr (RS == MAP_HLLC)
-        hllc_sel(L, pL, R, pR, D, gamma, gm1, ch, ch2, f);
+        hllc_sel<BB, VL, VR>(L, pL, R, pR, D, gamma, gm1, ch, ch2, f);
     else
-        rusanov_sel(L, pL, R, pR, D, gamma, ch, ch2, f);
+        rusanov_sel<BB, VL, VR>(L, pL, R, pR, D, gamma, ch, ch2, f);
 }
 
 }  // namespace mapk
