@@ -117,15 +117,20 @@ __global__ void __launch_bounds__(NT) k_step_mmc2(StepArgs a)
 
         auto al = [&](int v, int D) { return (v == BX + D || v == PSI) ? ch : alpha; };
         // split fluxes of a state w with the flux F along D into planes of
-        // stride n at index i (the flux is hidden from common-subexpression
-        // elimination: kept split fluxes would spill)
-        auto publish = [&](int D, const T (&w)[NV], T (&F)[NV], T *fp, T *fm, int n, int i) {
+        // stride n at index i, contractions written out (the flux is hidden
+        // from common-subexpression elimination: kept split fluxes would spill)
+        auto publish = [&](auto dc, const T (&w)[NV], T (&F)[NV], T *fp, T *fm, int n, int i) {
+#pragma clang fp contract(off)
+            constexpr int D = decltype(dc)::value;
 #pragma unroll
-            for (int v = 0; v < NV; v++) {
+            for (int v = 0; v < PSI; v++) {
                 asm volatile("" : "+v"(F[v]));
-                fp[v * n + i] = T(0.5) * (F[v] + al(v, D) * w[v]);
-                fm[v * n + i] = T(0.5) * (F[v] - al(v, D) * w[v]);
+                fp[v * n + i] = T(0.5) * Num<T>::fma_(al(v, D), w[v], F[v]);
+                fm[v * n + i] = T(0.5) * Num<T>::fma_(-al(v, D), w[v], F[v]);
             }
+            const T q = ch * w[PSI];
+            fp[PSI * n + i] = T(0.5) * Num<T>::fma_(w[BX + D], ch2, q);
+            fm[PSI * n + i] = T(0.5) * Num<T>::fma_(w[BX + D], ch2, -q);
         };
         // the predictor term dt/dx_D (h_{i+1/2} - h_{i-1/2}) of the own cell
         auto pred = [&](auto dc, T (&term)[NV]) {
@@ -190,9 +195,9 @@ __global__ void __launch_bounds__(NT) k_step_mmc2(StepArgs a)
         // ---- split fluxes of u; predictor on E: u~ = u - sum_d dt/dx_d (h_{i+1/2} - h_{i-1/2})
         T Fx[NV], Fy[NV];
         if (cell) {
-            ph.template flux<0, false>(u, ch2, Fx);
-            ph.template flux<1, false>(u, ch2, Fy);
-            publish(0, u, Fx, sfp, sfm, T2, c);
+            ph.template flux_fma<0>(u, ch2, Fx);
+            ph.template flux_fma<1>(u, ch2, Fy);
+            publish(X, u, Fx, sfp, sfm, T2, c);
 #pragma unroll
             for (int k = 0; k < 3; k++)
                 ub[k * T2 + c] = u[BX + k];
@@ -204,7 +209,7 @@ __global__ void __launch_bounds__(NT) k_step_mmc2(StepArgs a)
             pred(X, tx);
         __syncthreads();
         if (cell)
-            publish(1, u, Fy, sfp, sfm, T2, c);
+            publish(Y, u, Fy, sfp, sfm, T2, c);
         // the next block's records
         const int nxt = item + stride < end ? item + stride : item;
         hn = mmc_head(a, nxt);
@@ -215,12 +220,16 @@ __global__ void __launch_bounds__(NT) k_step_mmc2(StepArgs a)
         if (isE) {
             T ty[NV], Fty[NV];
             pred(Y, ty);
+            {
+                // (both terms rounded, whichever phase formed them)
+#pragma clang fp contract(off)
 #pragma unroll
-            for (int v = 0; v < NV; v++)
-                ut[v] = u[v] - (tx[v] + ty[v]);
-            ph.template flux<0, false>(ut, ch2, Ft);
-            ph.template flux<1, false>(ut, ch2, Fty);
-            publish(1, ut, Fty, stp, stm, E2, e);
+                for (int v = 0; v < NV; v++)
+                    ut[v] = u[v] - (tx[v] + ty[v]);
+            }
+            ph.template flux_fma<0>(ut, ch2, Ft);
+            ph.template flux_fma<1>(ut, ch2, Fty);
+            publish(Y, ut, Fty, stp, stm, E2, e);
         }
         if (cell) {
             const T *p = Uin + cell_src<2>(a.desc, hn.slot, x, y, 0);
@@ -235,9 +244,9 @@ __global__ void __launch_bounds__(NT) k_step_mmc2(StepArgs a)
         if (xin && yin)
             diff(Y, div[1]);
         if (cell)
-            publish(0, u, Fx, sfp, sfm, T2, c);
+            publish(X, u, Fx, sfp, sfm, T2, c);
         if (isE)
-            publish(0, ut, Ft, stp, stm, E2, e);
+            publish(X, ut, Ft, stp, stm, E2, e);
         __syncthreads();
         faces(X);
         __syncthreads();

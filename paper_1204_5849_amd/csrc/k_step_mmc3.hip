@@ -183,16 +183,22 @@ __global__ void __launch_bounds__(NTM, per_cu(sizeof(T))) k_step_mmc3(StepArgs a
 
         // split fluxes of a state along z, with the contractions written out:
         // the compiler's own differ between the march's first planes and the
-        // others, and the bits would depend on where a segment starts
-        auto split_z = [&](const T u[NV], T (&fp)[NV], T (&fm)[NV]) {
+        // others, and the bits would depend on where a segment starts.  RND:
+        // f+ rounds both of its terms (planes 0 and above of a march over the
+        // whole block)
+        auto split_z = [&](const T u[NV], T (&fp)[NV], T (&fm)[NV], bool rnd = false) {
 #pragma clang fp contract(off)
             T F[NV];
-            ph.flux_z(u, ch2, F);
+            ph.template flux_fma<2>(u, ch2, F);
 #pragma unroll
             for (int v = 0; v < NV; v++) {
-                fp[v] = T(0.5) * Num<T>::fma_(al(v, 2), u[v], F[v]);
+                const T w = al(v, 2) * u[v];
+                fp[v] = T(0.5) * (rnd ? F[v] + w : Num<T>::fma_(al(v, 2), u[v], F[v]));
                 fm[v] = T(0.5) * Num<T>::fma_(-al(v, 2), u[v], F[v]);
             }
+            const T w = ch * u[PSI];
+            fp[PSI] = T(0.5) * (rnd ? F[PSI] + w : Num<T>::fma_(u[BZ], ch2, w));
+            fm[PSI] = T(0.5) * Num<T>::fma_(u[BZ], ch2, -w);
         };
         // the thread index, with resistivity not known to be the same from
         // plane to plane: the indices formed from it are not kept (spills)
@@ -209,7 +215,7 @@ __global__ void __launch_bounds__(NTM, per_cu(sizeof(T))) k_step_mmc3(StepArgs a
 #pragma unroll
                 for (int v = 0; v < NV; v++)
                     u[v] = su[v * XSM + c];
-                ph.template flux<D, false>(u, ch2, F);
+                ph.template flux_fma<D>(u, ch2, F);
 #pragma unroll
                 for (int v = 0; v < NV; v++)
                     sF[v * XSM + c] = F[v];
@@ -232,7 +238,7 @@ __global__ void __launch_bounds__(NTM, per_cu(sizeof(T))) k_step_mmc3(StepArgs a
 #pragma unroll
             for (int v = 0; v < NV; v++)
                 u[v] = sut[v * XE + ei(qx, qy)];
-            ph.template flux<D, false>(u, ch2, F);
+            ph.template flux_fma<D>(u, ch2, F);
 #pragma unroll
             for (int v = 0; v < NV; v++)
                 sft[v * XE + ei(qx, qy)] = F[v];
@@ -240,7 +246,7 @@ __global__ void __launch_bounds__(NTM, per_cu(sizeof(T))) k_step_mmc3(StepArgs a
 #pragma unroll
                 for (int v = 0; v < NV; v++)
                     u[v] = sut[v * XE + xe];
-                ph.template flux<D, false>(u, ch2, F);
+                ph.template flux_fma<D>(u, ch2, F);
 #pragma unroll
                 for (int v = 0; v < NV; v++)
                     sft[v * XE + xe] = F[v];
@@ -311,8 +317,8 @@ __global__ void __launch_bounds__(NTM, per_cu(sizeof(T))) k_step_mmc3(StepArgs a
         load(up, z0);
         {
             T tmp[NV];
-            split_z(um, fpz_m1, tmp);
-            split_z(u0, fpz_0, fmz_0);
+            split_z(um, fpz_m1, tmp, z0 >= 2);
+            split_z(u0, fpz_0, fmz_0, z0 >= 1);
         }
 #pragma unroll
         for (int v = 0; v < NV; v++) {
@@ -417,7 +423,7 @@ __global__ void __launch_bounds__(NTM, per_cu(sizeof(T))) k_step_mmc3(StepArgs a
 
             // ---- (E) y and z terms, u~(p); the z face p-1/2 finishes plane p-1
             T fpz_p1[NV], fmz_p1[NV];
-            split_z(up, fpz_p1, fmz_p1);
+            split_z(up, fpz_p1, fmz_p1, true);
             T ut[NV];
 #pragma unroll
             for (int v = 0; v < NV; v++) {

@@ -93,6 +93,21 @@ __device__ __forceinline__ T limiter(T a, T b)
     }
 }
 
+// a0 b0 + a1 b1 + a2 b2.  I: the product that is rounded first, the others
+// entering by FMAs (the compiler's own choice, I = -1, depends on which of the
+// products another expression shares, and with it the last bits)
+template <int I, typename T>
+__device__ __forceinline__ T dot3(T a0, T b0, T a1, T b1, T a2, T b2)
+{
+    if constexpr (I < 0) {
+        return a0 * b0 + a1 * b1 + a2 * b2;
+    } else {
+#pragma clang fp contract(off)
+        using N = Num<T>;
+        return N::fma_(a2, b2, I == 0 ? N::fma_(a1, b1, a0 * b0) : N::fma_(a0, b0, a1 * b1));
+    }
+}
+
 template <typename T, bool MIXED>
 struct Phys {
     T gamma, gm1;
@@ -128,41 +143,42 @@ struct Phys {
         return pressure(u, ir, vx, vy, vz, me) > T(0);
     }
 
-    // flux<2, false> with the contractions written out, so that every inlined
+    // flux<D, false> with the contractions written out, so that every inlined
     // instance gives the same bits
-    __device__ __forceinline__ void flux_z(const T u[NV], T ch2, T f[NV]) const
+    template <int D>
+    __device__ __forceinline__ void flux_fma(const T u[NV], T ch2, T f[NV]) const
     {
 #pragma clang fp contract(off)
         using N = Num<T>;
         const T ir = N::rcp(u[RHO]);
         const T v[3] = {u[MX] * ir, u[MY] * ir, u[MZ] * ir};
         const T B[3] = {u[BX], u[BY], u[BZ]};
-        const T me = T(0.5) * N::fma_(B[2], B[2], N::fma_(B[1], B[1], B[0] * B[0]));
+        const T bb = dot3<D == 0 ? 0 : 1>(B[0], B[0], B[1], B[1], B[2], B[2]);
         T pr;
         if constexpr (MIXED) {
-            using D = Num<double>;
+            using E = Num<double>;
             const double m[3] = {(double)u[MX], (double)u[MY], (double)u[MZ]};
             const double b[3] = {(double)u[BX], (double)u[BY], (double)u[BZ]};
             double r = (double)ir;
-            r = r * D::fma_(-(double)u[RHO], r, 2.0);  // one Newton step on 1/rho
-            const double m2 = D::fma_(m[2], m[2], D::fma_(m[1], m[1], m[0] * m[0]));
-            const double b2 = D::fma_(b[2], b[2], D::fma_(b[1], b[1], b[0] * b[0]));
-            pr = (T)(gm1d * D::fma_(-0.5, D::fma_(m2, r, b2), (double)u[EN]));
+            r = r * E::fma_(-(double)u[RHO], r, 2.0);  // one Newton step on 1/rho
+            const double m2 = dot3<1>(m[0], m[0], m[1], m[1], m[2], m[2]);
+            const double b2 = dot3<1>(b[0], b[0], b[1], b[1], b[2], b[2]);
+            pr = (T)(gm1d * E::fma_(-0.5, b2, E::fma_(-0.5 * m2, r, (double)u[EN])));
         } else {
-            const T k2 = N::fma_(u[MZ], v[2], N::fma_(u[MY], v[1], u[MX] * v[0]));
-            pr = gm1 * (N::fma_(T(-0.5), k2, u[EN]) - me);
+            const T k2 = dot3<1>(u[MX], v[0], u[MY], v[1], u[MZ], v[2]);
+            pr = gm1 * N::fma_(T(-0.5), bb, N::fma_(T(-0.5), k2, u[EN]));
         }
-        const T pt = pr + me;
-        const T vb = N::fma_(v[2], B[2], N::fma_(v[1], B[1], v[0] * B[0]));
-        f[RHO] = u[MZ];
-        f[MX] = N::fma_(u[MX], v[2], -(B[0] * B[2]));
-        f[MY] = N::fma_(u[MY], v[2], -(B[1] * B[2]));
-        f[MZ] = N::fma_(u[MZ], v[2], -(B[2] * B[2])) + pt;
-        f[BX] = N::fma_(B[0], v[2], -(B[2] * v[0]));
-        f[BY] = N::fma_(B[1], v[2], -(B[2] * v[1]));
-        f[BZ] = u[PSI];
-        f[EN] = N::fma_(u[EN] + pt, v[2], -(B[2] * vb));
-        f[PSI] = ch2 * B[2];
+        const T pt = N::fma_(T(0.5), bb, pr);
+        const T vb = dot3<1>(v[0], B[0], v[1], B[1], v[2], B[2]);
+        f[RHO] = u[MX + D];
+#pragma unroll
+        for (int j = 0; j < 3; j++) {
+            const T m = N::fma_(u[MX + j], v[D], -(B[j] * B[D]));
+            f[MX + j] = j == D ? m + pt : m;
+            f[BX + j] = j == D ? u[PSI] : N::fma_(B[j], v[D], -(B[D] * v[j]));
+        }
+        f[EN] = N::fma_(u[EN] + pt, v[D], -(B[D] * vb));
+        f[PSI] = ch2 * B[D];
     }
 
     // EGLM flux along D (MHD-1..MHD-5); returns |v_D| + c_f,D if SPEED
@@ -226,21 +242,6 @@ template <typename T>
 __device__ __forceinline__ bool admissible_w(const T u[NV], const Prim<T> &w)
 {
     return u[RHO] > T(0) && w.p > T(0);
-}
-
-// a0 b0 + a1 b1 + a2 b2.  I: the product that is rounded first, the others
-// entering by FMAs (the compiler's own choice, I = -1, depends on which of the
-// products another expression shares, and with it the last bits)
-template <int I, typename T>
-__device__ __forceinline__ T dot3(T a0, T b0, T a1, T b1, T a2, T b2)
-{
-    if constexpr (I < 0) {
-        return a0 * b0 + a1 * b1 + a2 * b2;
-    } else {
-#pragma clang fp contract(off)
-        using N = Num<T>;
-        return N::fma_(a2, b2, I == 0 ? N::fma_(a1, b1, a0 * b0) : N::fma_(a0, b0, a1 * b1));
-    }
 }
 
 // EGLM flux along dimension d from a state and its primitives.  d may differ

@@ -34,6 +34,9 @@ def configs():
         for rs in ("rusanov", "hllc"):
             for scheme, lim in (("lf", "minmod"), ("lf", "vanleer"), ("lf", "paper"), ("weno", "minmod")):
                 yield 3, scheme, lim, rs, eta
+        for ndim in (2, 3):
+            for lim in ("minmod", "vanleer", "paper"):
+                yield ndim, "mmc", lim, "rusanov", eta
 
 
 def record(ndim, scheme, limiter, riemann, eta):
