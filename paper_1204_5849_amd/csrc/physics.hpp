@@ -24,6 +24,11 @@ struct Num<double> {
     static __device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
     static __device__ __forceinline__ double max_(double a, double b) { return __builtin_fmax(a, b); }
     static __device__ __forceinline__ double min_(double a, double b) { return __builtin_fmin(a, b); }
+    // r, or NaN where a is NaN
+    static __device__ __forceinline__ double nan_as(double a, double r)
+    {
+        return __hiloint2double(__builtin_isnan(a) ? 0x7ff80000 : __double2hiint(r), __double2loint(r));
+    }
     // b where the mask m is 0, a where it is all ones
     static __device__ __forceinline__ double pick(unsigned m, double a, double b)
     {
@@ -61,11 +66,14 @@ __device__ __forceinline__ double kappa_of(double kappa0, int khalf, double T)
 // minmod(a,b) = sgn(a) max(0, min(|a|, sgn(a) b))  (eq. minmod), as the
 // smaller of two positive values plus the larger of two negative ones (one of
 // the two terms is zero): five FP64 instructions where the sign, its products
-// and their selects took about fifteen
+// and their selects took about fifteen, and two that keep a NaN in a, which
+// the minima and maxima pass over (a NaN in b leaves a, as in the formula)
 template <typename T>
 __device__ __forceinline__ T lim_minmod(T a, T b)
 {
-    return Num<T>::max_(Num<T>::min_(a, b), T(0)) + Num<T>::min_(Num<T>::max_(a, b), T(0));
+    using N = Num<T>;
+    const T r = N::max_(N::min_(a, b), T(0)) + N::min_(N::max_(a, b), T(0));
+    return N::nan_as(a, r);
 }
 
 // in FP32 the same value is the median of (a, b, 0): the smaller magnitude
@@ -285,9 +293,12 @@ __device__ __forceinline__ T fast_sel(const T u[NV], const Prim<T> &w, int d, T 
     const T b2 = w.bb * w.ir;
     const T s = a2 + b2;
     const T Bd = d == 0 ? u[BX] : (d == 1 ? u[BY] : u[BZ]);
-    const T disc = Num<T>::max_(s * s - T(4) * a2 * (Bd * Bd) * w.ir, T(0));
-    const T cf2 = T(0.5) * (s + Num<T>::sqrt_(disc));
-    return Num<T>::sqrt_(Num<T>::max_(cf2, T(0)));
+    // (comparisons, not maxima: a NaN stays one)
+    T disc = s * s - T(4) * a2 * (Bd * Bd) * w.ir;
+    disc = disc < T(0) ? T(0) : disc;
+    T cf2 = T(0.5) * (s + Num<T>::sqrt_(disc));
+    cf2 = cf2 < T(0) ? T(0) : cf2;
+    return Num<T>::sqrt_(cf2);
 }
 
 // |v_d| + c_f,d from a state and its primitives (d as in flux_sel)

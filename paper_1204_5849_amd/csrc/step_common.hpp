@@ -83,7 +83,7 @@ __device__ __forceinline__ void rusanov_sel(const T L[NV], T pL, const T R[NV], 
     flux_sel<VL>(L, wL, d, ch2, FL);
     flux_sel<VR>(R, wR, d, ch2, FR);
     const T sL = speed_sel(L, wL, d, gamma), sR = speed_sel(R, wR, d, gamma);
-    const T al = Num<T>::max_(sL, sR);
+    const T al = sL > sR ? sL : sR;  // (the right one if either is NaN)
 #pragma unroll
     for (int k = 0; k < NV; k++) {
         const T ak = (k == BX + d || k == PSI) ? ch : al;
