@@ -1,25 +1,36 @@
 // fp64.hpp -- FP64 reciprocal, quotient and square root from the hardware
-// estimates and Newton steps on FMAs.
+// estimates: Newton's iteration for the reciprocal, the coupled iteration for
+// the root and its reciprocal (Goldschmidt's), each ended by a correction with
+// the exact FMA residual.
 //
 // The estimates (v_rcp_f64, v_rsq_f64) are good to 4.6e-8 and 5.3e-8
-// (measured); two Newton steps on the exact FMA residual leave the correctly
-// rounded reciprocal, one step and one residual correction the correctly
-// rounded root.  Over 8 M arguments each in 2^+-40, 2^+-500 and 2^+-1000 all
-// three equal the compiler's IEEE division and square root bit for bit,
-// without its operand scaling; v_div_fixup gives zeros, infinities and NaN
-// their IEEE results.  Throughput per wave64 instruction on one SIMD (4 waves): 1/x 58 ->
-// 36 cycles, sqrt 75 -> 48 cycles.
+// (measured); after one more step on the residual the results are the correctly
+// rounded ones.  Over 8 M arguments each in 2^+-40, 2^+-500 and 2^+-1000
+// (quotients: divisors of these, quotients in 2^+-1000) all three equal the
+// compiler's IEEE division and square root bit for bit, without its operand
+// scaling, and v_div_fixup gives zero, infinite and NaN arguments their IEEE
+// results.  Without the scaling they are not IEEE's at the ends of the range:
+//   rcp64   subnormal results are not correctly rounded
+//   div64   NaN for a divisor below 2^-1024 and for a quotient that overflows;
+//           subnormal quotients are not correctly rounded
+//   sqrt64  a subnormal argument's root is good to 1e-15
+// so divisors that are not a density, a speed or a sum of WENO weights (a
+// squared field, an estimator's denominator) take the compiler's division.
+// Throughput per wave64 instruction on one SIMD (4 waves): 1/x 58 -> 36 cycles,
+// sqrt 75 -> 48 cycles.
 #pragma once
 
 #include <hip/hip_runtime.h>
 
 namespace mapk {
 
-// 1/x to the last bit before the special cases
+// 1/x to the last bit before the special cases.  The first step is a product,
+// so that an estimate that overflowed (x below 2^-1024) stays infinite: as a
+// sum it would be inf - inf
 __device__ __forceinline__ double rcp_newton(double x)
 {
     double r = __builtin_amdgcn_rcp(x);
-    r = __builtin_fma(r, __builtin_fma(-x, r, 1.0), r);
+    r = r * __builtin_fma(-x, r, 2.0);
     return __builtin_fma(r, __builtin_fma(-x, r, 1.0), r);
 }
 

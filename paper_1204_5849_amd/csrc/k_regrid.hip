@@ -48,7 +48,9 @@ __device__ __forceinline__ double est_cell(const EstArgs &a, int i, double v, do
     const double d1 = 0.5 * sqrt(3.0) * sqrt64(s1);
     const double d2 = sqrt64(s2);
     const double av = fabs(v) + a.est.eps[i];
-    return (div64(a.est.bias * d1, av) + div64((1.0 - a.est.bias) * d2, d1 + a.est.filt * av)) * scale;
+    // (eps may be 0 and the value tiny: IEEE division, which gives infinity where
+    // the quotient overflows)
+    return (a.est.bias * d1 / av + (1.0 - a.est.bias) * d2 / (d1 + a.est.filt * av)) * scale;
 }
 
 // the largest `best` of the workgroup's threads
