@@ -239,7 +239,12 @@ map_status run_cfl(map_ctx *c, const void *U, map_dt *dt_out, hipStream_t s,
 // whether the 2-D LF update forms the next cycle's CFL maxima of the leaves
 // without parent that no reflux changes (map_launch::cfl_in_update); the
 // automatic rule takes batched launches over at least 4 leaves per CU (a
-// launch per block runs each update alone, latency-bound)
+// launch per block runs each update alone, latency-bound).  An update that
+// forms them runs whole blocks (step_lseg), so up to some size a caller who
+// sets it to 0 gains more from row segments than from the saved pass: us per
+// cycle on 256 CUs with it off / on (better workgroup shape), FP64 1024 leaves
+// 60 / 88, 1600 63 / 89, 2304 96 / 91, 4096 174 / 169; FP32 1024 41 / 70, 2304
+// 58 / 85, 3136 63 / 86, 4096 90 / 88
 bool cfl_in_update(const map_ctx *c)
 {
     if (c->nd != 2 || c->p.scheme != MAP_LF)
@@ -1038,17 +1043,23 @@ map_status map_autotune(map_ctx *c, void *U, int *chosen, void *stream)
                 g.push_back(c->ncu * m);
         return g;
     };
-    // the update: workgroup shape x persistent grid
+    // the update as the cycles launch it (LF: with the next cycle's CFL maxima
+    // where they are formed there, and then not in segments): workgroup shape x
+    // persistent grid below its work items
+    const bool cfl_next = c->p.scheme == MAP_LF && chain_dt(c);
     int best_shape = 0, best_step = 0;
     float best_t = 1e30f;
     const int nshapes = has_step_shapes(c) ? 2 : 1;
     for (int shape = 0; shape < nshapes; shape++) {
         c->step_shape = shape;
         const int bpw = step_blocks_per_group(c->nd, c->p.scheme, shape);
-        for (int g : grids((c->nleaves + bpw - 1) / bpw)) {
+        const int groups = (c->nleaves + bpw - 1) / bpw;
+        for (int g : grids(groups << step_lseg(c, groups, cfl_next && cfl_in_update(c)))) {
             c->grid_step = g;
             const int sch = c->p.scheme == MAP_WENO ? SCH_WENO1 : SCH_LF;
-            float t = time_it([&] { return run_step_kernel(c, sch, U, shadow(c), nullptr, dt, s); });
+            float t = time_it([&] {
+                return run_step_kernel(c, sch, U, shadow(c), nullptr, dt, s, cfl_next);
+            });
             if (faster(t, best_t)) {
                 best_t = t;
                 best_shape = shape;

@@ -188,3 +188,24 @@ def test_segments_of_a_3d_march(precision):
         many = run(copies)
         for s in (0, copies // 2, copies - 1):
             assert np.array_equal(many[s * 16:(s + 1) * 16], one), f"{copies} copies, simulation {s}"
+
+
+def test_autotune_times_the_update_that_cycles_run():
+    """1024 leaves, where the LF update forms the next cycle's CFL maxima and so
+    runs whole blocks: the autotuner times that update, which counts a planted
+    non-finite cell in each launch, and not the segmented one, which leaves it
+    to the CFL pass (one count, of the pass that the autotuner starts with)."""
+    sd = W.SimDesc(lo=(0, 0, 0), hi=(1, 1, 1), nbase=(32, 32, 1), bc=(("periodic",) * 2,) * 3)
+    w = W.Workload(name="tuned", ndim=2, sims=[sd], keys=W.base_keys(0, sd.nbase, 2), ic=_ic, scheme="lf",
+                   precision="fp32")
+    s = Simulation(w, device="cuda:0")
+    s.load_initial()
+    cfg = s.launch_config()
+    assert cfg["cfl_in_update_on"] == (1 if len(w.keys) >= 4 * torch.cuda.get_device_properties(0).multi_processor_count else 0)
+    s.U[5, 0, 0, 2 + 8, 2 + 8] = float("nan")
+    torch.cuda.synchronize()
+    s.flags()
+    before = s.flags()[1][3]
+    s.autotune()
+    n = s.flags()[1][3] - before
+    assert n > 1 if cfg["cfl_in_update_on"] else n == 1
