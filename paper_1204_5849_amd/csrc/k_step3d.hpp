@@ -3,10 +3,11 @@
 // one stage of WENO with TVD Runge-Kutta 2 (Sec. 3.3), with the EGLM source
 // terms (Sec. 2), uniform resistivity (Sec. 3.5) and exact psi damping.
 //
-// Schedule (gfx950): one block per workgroup of 15 waves, one workgroup per
-// CU (FP32: 130-145 KB of LDS), marching along z one plane per iteration.  Waves 0-3, 4-7 and 8-11 own
-// the 16 x 16 columns for x, y and z; waves 12-14 own the ring of 64 cells
-// just outside the interior for the same three dimensions.  A thread forms
+// Schedule (gfx950): one block per workgroup of 15 waves, one workgroup per CU
+// (LDS: LF 128.6 KB, WENO 122.2 KB, 8 KB more with resistivity), marching along
+// z one plane per iteration.  Waves 0-3, 4-7 and 8-11 own the 16 x 16 columns
+// for x, y and z; waves 12-14 own the ring of 64 cells just outside the
+// interior for the same three dimensions.  A thread forms
 // its cell's slope, half-step flux pair, face states and face flux along its
 // own dimension only, so it keeps to 128 registers and each SIMD has four
 // waves to issue from (an FP32 add, multiply or FMA issues every 2 cycles from
@@ -63,7 +64,7 @@ constexpr int PTD = XSD * PD;              // padded tile
 constexpr int NCD = NB * NB;               // columns
 constexpr int NRD = 4 * NB;                // ring cells of a plane
 constexpr int NCELLD = NCD + NRD;          // cells with a predictor
-constexpr int NOD = 4 * PD + 4;            // outer ring cells and ring corners (load only)
+constexpr int NOD = 4 * PD;                // outer ring cells and ring corners (load only)
 constexpr int OPWD = NOD / 2;              // of them per x or y ring wave
 constexpr int NLDD = NRD + NOD;            // cells loaded one by one
 static_assert(NB == 16 && OPWD <= 64, "lane layout assumes 16^3 blocks");
