@@ -209,3 +209,31 @@ def test_autotune_times_the_update_that_cycles_run():
     s.autotune()
     n = s.flags()[1][3] - before
     assert n > 1 if cfg["cfl_in_update_on"] else n == 1
+
+
+@pytest.mark.parametrize("ndim,scheme,precision", [(2, "lf", "fp32"), (2, "mmc", "fp64"), (2, "mmc", "fp32"),
+                                                   (3, "lf", "fp32"), (3, "lf", "fp64"), (3, "weno", "fp32"),
+                                                   (3, "mmc", "fp64"), (3, "mmc", "fp32")])
+def test_small_and_uneven_grids(ndim, scheme, precision):
+    """Persistent grids that stride (fewer workgroups than work items), below and
+    not a multiple of the eight XCDs: the state of the default grid bit for bit."""
+    sd = W.SimDesc(lo=(0, 0, 0), hi=(1, 1, 1), nbase=(3, 2, 2 if ndim == 3 else 1),
+                   bc=(("periodic",) * 2, ("outflow",) * 2, ("periodic",) * 2))
+    keys = []
+    for sim in range(8 if ndim == 2 else 3):
+        base = W.base_keys(sim, sd.nbase, ndim)
+        keys += [base, W.children_of(base[1:2], ndim)]
+    w = W.Workload(name="grids", ndim=ndim, sims=[sd] * (8 if ndim == 2 else 3), keys=np.concatenate(keys),
+                   ic=_ic, scheme=scheme, eta=1e-3, precision=precision, glm_mode="fastspeed")
+    out = []
+    for grid in (0, 1, 3, 11, 24):
+        s = Simulation(w, device="cuda:0")
+        s.load_initial()
+        s.set_launch_config(grid_step=grid)
+        s.advance(2)
+        s.sync()
+        inner = slice(2, -2) if ndim == 3 else slice(None)
+        out.append((s.state_by_key()[:, :, inner, 2:-2, 2:-2], s.flags()[1]))
+    assert np.isfinite(out[0][0]).all()
+    for U, cnt in out[1:]:
+        assert np.array_equal(U, out[0][0]) and cnt == out[0][1]
