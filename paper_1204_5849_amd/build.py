@@ -12,12 +12,12 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libmap.so")
-SOURCES = ["plan.cpp", "regrid.cpp", "api.hip", "k_step2.hip", "k_step3.hip", "k_step3_ilp.hip",
+SOURCES = ["plan.cpp", "regrid.cpp", "api.hip", "k_step2.hip", "k_step3.hip", "k_step3_lf32.hip",
            "k_step_mmc.hip", "k_step_mmc3.hip", "k_aux.hip", "k_regrid.hip", "k_cond.hip"]
 # per-source options, measured per kernel on MI355X: the FP32 3-D LF update
 # without loop strength reduction (1 % faster with Rusanov, 8 % with HLLC; the
 # WENO stages 3-5 % slower that way)
-EXTRA = {"k_step3_ilp.hip": ["-mllvm", "-disable-lsr"]}
+EXTRA = {"k_step3_lf32.hip": ["-mllvm", "-disable-lsr"]}
 ARCH = os.environ.get("MAP_OFFLOAD_ARCH", "gfx950")
 
 

@@ -1,5 +1,5 @@
 // k_step3.hip -- launches of the 3-D block update: the FP32 LF step is
-// instantiated in k_step3_ilp.hip, every other instance here.
+// instantiated in k_step3_lf32.hip, every other instance here.
 #include "k_step3.hpp"
 
 namespace mapk {

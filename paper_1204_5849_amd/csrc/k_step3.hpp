@@ -40,7 +40,7 @@
 //     read from U_base at the cell itself, then damps psi, and the reflux
 //     face fluxes become the mean of both stages' fluxes.
 // A persistent grid strides over the leaf list.  The FP32 LF instances are
-// compiled in k_step3_ilp.hip, the others in k_step3.hip: they take different
+// compiled in k_step3_lf32.hip, the others in k_step3.hip: they take different
 // compiler options (see the build script).
 #pragma once
 

@@ -1,4 +1,4 @@
-// k_step3_ilp.hip -- the FP32 instances of the 3-D TVD-LF step (one per limiter
+// k_step3_lf32.hip -- the FP32 instances of the 3-D TVD-LF step (one per limiter
 // and face flux, with and without resistivity).  They run faster without
 // LLVM's loop strength reduction, whose per-variable address registers spill
 // at 128 registers per lane; the others stay in k_step3.hip with the defaults
