@@ -386,7 +386,6 @@ map_status run_reflux(map_ctx *c, void *U, const map_dt *dt, hipStream_t s, int 
     a.lvl_dx = dptr<double>(c, c->ws.lvl_dx);
     a.fbuf = c->wsp + c->ws.fbuf;
     a.nitems = (int)c->reflux_slots.size();
-    a.vsplit = !a.eonly && c->nd == 3 && a.nitems < c->ncu;
     HIPCHK(launch_reflux(c->nd, fp64(c), a, s));
     return MAP_OK;
 }

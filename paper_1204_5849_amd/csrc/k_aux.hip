@@ -643,13 +643,18 @@ __global__ void __launch_bounds__(nt_restrict(NDIM, PC)) k_restrict(RestrictArgs
 }
 
 // ---- reflux: the faces of a coarse leaf in a fixed order (two faces share
-// their edge cells).  Variables do not meet, so a list shorter than the CUs
-// takes a workgroup per variable of a leaf (a.vsplit), which cuts a face from
-// nine passes of 256 cells to one: 31.6 -> 24.6 us on the blast's 120 leaves,
-// 18.9 -> 17.7 on 24, but 22.2 -> 24.8 on 672, where the chip was full
+// their edge cells), a workgroup per leaf.  Bound by latency: a short list of
+// leaves, and per face a chain of loads.  In 3-D a face has a cell per thread,
+// which loads all nine variables before it forms the first: one wait instead
+// of nine, 30.4 -> 23.1 us (FP32) and 37.4 -> 29.2 us (FP64) after an update on
+// 120 leaves, 9.3 -> 7.4 and 10.4 -> 8.2 on 32, 24.6 -> 25.2 and 31.4 -> 31.6
+// on 672, where the waves of other leaves had covered the waits.  A workgroup
+// per variable of a leaf instead takes 24.0 and 26.7 on the 120, 16.5 and 16.7
+// on the 32.
 template <int NDIM, typename T, bool EO>
 __global__ void __launch_bounds__(NTA) k_reflux(RefluxArgs a)
 {
+    using V = typename Pair<T>::V;
     constexpr int P = FG<NDIM>::P;
     constexpr int FC = NDIM == 3 ? NB * NB : NB;
     constexpr int K0 = VarRange<EO>::K0, K1 = VarRange<EO>::K1;
@@ -657,10 +662,7 @@ __global__ void __launch_bounds__(NTA) k_reflux(RefluxArgs a)
     const T *fb = (const T *)a.fbuf;
     if (EO && sub_idle(a.dt, a.nsims, a.sub))
         return;
-    const int nsh = a.vsplit ? K1 - K0 : 1;  // workgroups per leaf
-    for (int it = blockIdx.x; it < a.nitems * nsh; it += gridDim.x) {
-        const int item = it / nsh;
-        const int v0 = a.vsplit ? K0 + it - item * nsh : K0, v1 = a.vsplit ? v0 + 1 : K1;
+    for (int item = blockIdx.x; item < a.nitems; item += gridDim.x) {
         const int slot = a.slots[item];
         const BlockRec br = a.blk[slot];
         if (EO && sub_inactive(a.dt, br.sim, a.sub))
@@ -672,35 +674,46 @@ __global__ void __launch_bounds__(NTA) k_reflux(RefluxArgs a)
             const RefluxRec r = a.recs[e];
             const T dtdx = (T)(dtv / dxp[r.dim]);
             const int t1 = r.dim == 0 ? 1 : 0, t2 = r.dim == 2 ? 1 : 2;
-            for (int idx = threadIdx.x; idx < FC * (v1 - v0); idx += NTA) {
-                const int k = v0 + idx / FC, tt = idx - (k - v0) * FC;
-                const int ta = tt % NB, tb = NDIM == 3 ? tt / NB : 0;
-                T f[4];
-                const int nf = NDIM == 3 ? 4 : 2;
-#pragma unroll
-                for (int o = 0; o < 4; o++) {
-                    if (o >= nf)
-                        break;
-                    const int fa = 2 * ta + (o & 1);
-                    const int fbb = NDIM == 3 ? 2 * tb + ((o >> 1) & 1) : 0;
-                    const int which = (fa / NB) | ((fbb / NB) << 1);
-                    const int tl = (fbb % NB) * NB + (fa % NB);
-                    f[o] = fb[((size_t)r.fb_fine[which] * NV + k) * FC + (NDIM == 3 ? tl : fa % NB)];
-                }
-                T mean;
-                if constexpr (NDIM == 3)
-                    mean = ((f[0] + f[1]) + (f[2] + f[3])) * T(0.25);
-                else
-                    mean = (f[0] + f[1]) * T(0.5);
-                const T fcv = fb[((size_t)r.fb_coarse * NV + k) * FC + tt];
-                const T delta = dtdx * (fcv - mean);
-                int loc[3] = {0, 0, 0};
-                loc[r.dim] = r.side ? NB - 1 : 0;
+            int loc[3] = {0, 0, 0};
+            loc[r.dim] = r.side ? NB - 1 : 0;
+            if constexpr (NDIM == 3) {
+                static_assert(FC == NTA && NB % 2 == 0, "a cell of the face per thread");
+                const int tt = threadIdx.x, ta = tt % NB, tb = tt / NB;
+                const int fa = 2 * ta, fbb = 2 * tb;
+                const int which = (fa / NB) | ((fbb / NB) << 1);
+                const int tl = (fbb % NB) * NB + (fa % NB);  // even: the pair is aligned
+                const T *ff = fb + (size_t)r.fb_fine[which] * NV * FC + tl;
+                const T *fc = fb + (size_t)r.fb_coarse * NV * FC + tt;
                 loc[t1] = ta;
-                if (t2 < NDIM)
-                    loc[t2] = tb;
-                T *cell = ub + (size_t)k * P + lin<NDIM>(loc[0], loc[1], loc[2]);
-                *cell = r.side ? *cell + delta : *cell - delta;
+                loc[t2] = tb;
+                T *cell = ub + lin<NDIM>(loc[0], loc[1], loc[2]);
+                V f0[K1], f1[K1];
+                T fcv[K1], u[K1];
+#pragma unroll
+                for (int k = K0; k < K1; k++) {
+                    f0[k] = *reinterpret_cast<const V *>(ff + k * FC);
+                    f1[k] = *reinterpret_cast<const V *>(ff + k * FC + NB);
+                    fcv[k] = fc[k * FC];
+                    u[k] = cell[(size_t)k * P];
+                }
+#pragma unroll
+                for (int k = K0; k < K1; k++) {
+                    const T mean = ((f0[k].x + f0[k].y) + (f1[k].x + f1[k].y)) * T(0.25);
+                    const T delta = dtdx * (fcv[k] - mean);
+                    cell[(size_t)k * P] = r.side ? u[k] + delta : u[k] - delta;
+                }
+            } else {
+                for (int idx = threadIdx.x; idx < FC * (K1 - K0); idx += NTA) {
+                    const int k = K0 + idx / FC, ta = idx - (k - K0) * FC;
+                    const int fa = 2 * ta;
+                    const T *ff = fb + ((size_t)r.fb_fine[fa / NB] * NV + k) * FC + fa % NB;
+                    const T mean = (ff[0] + ff[1]) * T(0.5);
+                    const T fcv = fb[((size_t)r.fb_coarse * NV + k) * FC + ta];
+                    const T delta = dtdx * (fcv - mean);
+                    loc[t1] = ta;
+                    T *cell = ub + (size_t)k * P + lin<NDIM>(loc[0], loc[1], loc[2]);
+                    *cell = r.side ? *cell + delta : *cell - delta;
+                }
             }
             __syncthreads();  // faces of one block may share edge cells
         }
@@ -1075,8 +1088,7 @@ hipError_t launch_reflux(int ndim, bool fp64, const RefluxArgs &a, hipStream_t s
 {
     if (a.nitems <= 0)
         return hipSuccess;
-    const int n = a.vsplit && !a.eonly ? a.nitems * NV : a.nitems;
-    const int g = a.eonly && n > SUB_GRID ? SUB_GRID : n;
+    const int g = a.eonly && a.nitems > SUB_GRID ? SUB_GRID : a.nitems;
     DISPATCH_EO(ndim, fp64, a.eonly, k_reflux, dim3(g), dim3(NTA), 0, s, a);
     return hipGetLastError();
 }

@@ -88,7 +88,7 @@ struct RefluxArgs {
     const map_dt *dt;
     const double *lvl_dx;
     const void *fbuf;
-    int nitems, vsplit;     // leaves; whether each variable of a leaf takes a workgroup
+    int nitems;
     int eonly, sub, nsims;  // conduction sub-step: energy only, dt_sub
 };
 
