@@ -467,7 +467,8 @@ __global__ void __launch_bounds__(NTA) k_prolong_blocks(FillArgs a)
 // child with LDS atomics on the bit patterns (the speeds are finite and
 // non-negative, so those order like the values).
 // PC: per child, one parent cell per thread (512 threads in 3-D, 64 in 2-D):
-// 30.8 -> 26.1 us for 256 FP64 children, 26.4 -> 19.5 for 256 FP32 ones
+// with CFL and the layers below 28.5 -> 23.0 us for 256 FP64 children,
+// 20.4 -> 15.5 for 256 FP32 ones
 constexpr int nt_restrict(int ndim, bool pc)
 {
     return pc ? (ndim == 3 ? NB * NB * NB / 8 : NB * NB / 4) : NTA;
@@ -494,9 +495,30 @@ __global__ void __launch_bounds__(nt_restrict(NDIM, PC)) k_restrict(RestrictArgs
     // or two (FP64) waves per SIMD (140 and 194 registers; 106 and 152 now),
     // too few to load while others form speeds: two cycles of 1464 FP32 leaves
     // 1228 -> 1201 us, of 19264 28.9 -> 28.65 ms.  Fewer registers by launch
-    // bounds (96 and 128) spill and are no faster
+    // bounds (96 and 128) spill and are no faster.  Without CFL there is nothing
+    // to hold: a variable is stored when its cells are summed, 13.4 -> 11.1 us
+    // for 256 FP32 children, 177 -> 167 us for 864 parents, 333 -> 312 in FP64
+    // (2-D FP64 15.3 -> 14.6 us for 1340 parents; 2-D FP32 stores them together,
+    // 10.9 against 11.8 us)
+    constexpr bool STREAM = !CFL && (NDIM == 3 || sizeof(T) == 8);
     auto restrict_cell = [&](T *ub, const T *cu, int c0, int d, bool leafc, double &mh, unsigned &bad,
                              unsigned &nonfin) {
+        if constexpr (STREAM) {
+#pragma unroll
+            for (int k = K0; k < K1; k++) {
+                const T *q = cu + (size_t)k * P + c0;
+                const V r0 = *reinterpret_cast<const V *>(q);
+                const V r1 = *reinterpret_cast<const V *>(q + PD);
+                T v = (r0.x + r0.y) + (r1.x + r1.y);
+                if constexpr (NDIM == 3) {
+                    const V r2 = *reinterpret_cast<const V *>(q + PD * PD);
+                    const V r3 = *reinterpret_cast<const V *>(q + PD * PD + PD);
+                    v = v + ((r2.x + r2.y) + (r3.x + r3.y));
+                }
+                ub[(size_t)k * P + d] = v * T(NDIM == 3 ? 0.125 : 0.25);
+            }
+            return;
+        }
         constexpr int NL = NDIM == 3 ? 2 : 1;
         T sum[K1];
         auto layer = [&](int h) {
