@@ -127,7 +127,12 @@ map_status run_fill(map_ctx *c, void *U, hipStream_t s, bool all, int eonly_sub 
             a.nitems = 1;
             HIPCHK(launch_fill_copy(c->nd, fp64(c), a, 1, s));
         }
-    } else if (all && c->nd == 3) {
+    } else if (all && c->nd == 3 && 3ll * ncopy > 4ll * c->ncu) {
+        // fewer blocks leave its items too few for the chip, or its chunks no
+        // use: there the copies in shares of a block are faster (1 block 38.5 ->
+        // 4.6 us, 64 FP32 blocks 16.0 -> 12.6, 216 FP64 46.9 -> 45.1, 320 FP32
+        // 43.0 -> 41.2), and from here on slower (343 FP64 74.0 -> 76.1, 512
+        // FP32 61.3 -> 65.8)
         a.slot_end = ncopy;
         HIPCHK(launch_fill_all3(fp64(c), a, c->ncu, s));
     } else if (ncopy > 0) {

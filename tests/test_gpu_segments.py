@@ -149,6 +149,25 @@ def test_complete_frames_3d(copies, precision):
 
 
 @pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_complete_frames_3d_where_the_path_changes(precision):
+    """Lists up to 4/3 of the CUs are copied in shares of a block, longer ones by
+    variable over chunks: 336 and 352 blocks lie on either side with 256 CUs, and
+    one block that is its own neighbour takes the most shares."""
+    for copies in (21, 22):
+        test_complete_frames_3d(copies, precision)
+    sd = W.SimDesc(lo=(0, 0, 0), hi=(1, 1, 1), nbase=(1, 1, 1), bc=(("periodic",) * 2,) * 3)
+    w = W.Workload(name="frame", ndim=3, sims=[sd], keys=W.base_keys(0, sd.nbase, 3), ic=_ic,
+                   scheme="lf", precision=precision, glm_mode="fastspeed")
+    s = Simulation(w, device="cuda:0")
+    s.load_initial()
+    s.fill()
+    s.sync()
+    u = s.U[0].cpu().numpy()
+    inner = u[:, 2:-2, 2:-2, 2:-2]
+    assert np.array_equal(u, np.pad(inner, ((0, 0), (2, 2), (2, 2), (2, 2)), mode="wrap"))
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
 def test_segments_of_a_3d_march(precision):
     """MacCormack with resistivity on one tree (15 leaves, each march in 8
     segments of 2 planes) and on 20, 40 and 150 copies of it: 37 or 38 leaves
