@@ -86,9 +86,8 @@ bool fp64(const map_ctx *c) { return c->p.precision == MAP_FP64; }
 // how the copies of n frames are cut into work items: blocks per item (2-D,
 // 144 ghost cells each), items per block (3-D, 3904 cells).  A thread's cells
 // are a chain of descriptor, source and store, so short lists take as many
-// items as give every thread one cell: 18.6 -> 5.5 us
-// for the 88 frames of a 2-D tree, 37 -> 22 us for the blast's 128, 29.6 ->
-// 10.4 us for 32 FP64 ones
+// items as give every thread one cell: 18.6 -> 5.5 us for the 88 frames of a
+// 2-D tree, 37 -> 22 us for the blast's 128, 29.6 -> 10.4 us for 32 FP64 ones
 void fill_split(const map_ctx *c, int n, int &bpw, int &parts)
 {
     bpw = c->nd == 3 || n < 16 * c->ncu ? 1 : 16;

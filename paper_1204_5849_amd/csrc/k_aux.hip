@@ -157,11 +157,12 @@ __global__ void __launch_bounds__(NTA) k_fill_copy(FillArgs a)
 // so a block per item fetched each state line several times (14.3 GB for a
 // 6.3 GB state: the 256 blocks in flight on an XCD do not fit its L2).  A
 // chunk of neighbouring blocks is walked one variable at a time instead,
-// whose tiles do fit: 11.5 GB, and 3612 -> 3291 us for the
-// 22016-block FP32 state, 1715 -> 1509 us for 5440 FP64 blocks, 275 -> 250 us
-// for 1024 FP32 blocks.  Chunks of 16 and 64 blocks take 3303 and 3358 us,
-// 2 or 8 workgroups per CU 3705 and 3613, stores from the block that holds the
-// values into its neighbours' frames (whole lines read, pieces stored) 4890.
+// whose tiles do fit: 11.5 GB, and 3607 -> 3288 us for the 22016-block FP32
+// state (FP64 7200 -> 6208), 1581 -> 1361 us for 5440 FP64 blocks, 138 -> 135
+// for 1000 FP32 ones after an update.  Chunks of 16 and 64 blocks take 3303 and
+// 3358 us, 2 or 8 workgroups per CU 3705 and 3613, stores from the block that
+// holds the values into its neighbours' frames (whole lines read, pieces
+// stored) 4890.
 // Bound by the pieces of lines it moves: 16-byte x ghosts in 11.5 GB read and
 // 4.3 GB written for 3.1 GB of ghosts.
 // The cells' order and offsets are the same for every block: a table in LDS

@@ -23,9 +23,10 @@
 //     four waves, 1.7 of five or six, 2.1 of eight; 80 registers: 2.6 of six).
 //     One window cell per thread, the x fluxes and energies in registers
 //     (50 -> 41 KB of LDS) and at most 80 registers.  4768 FP32 leaves along
-//     the field: 600 -> 410 us a sub-step, together with quotients and roots
-//     from the hardware estimates and neighbouring blocks on one XCD (fetch
-//     2.9 -> 1.7 GB);
+//     the field: 600 -> 440 us a sub-step, together with roots and reciprocals
+//     from the hardware estimates (the quotient by |B|^2, which may be tiny, is
+//     an IEEE division: 410 us without) and neighbouring blocks on one XCD
+//     (fetch 2.9 -> 1.7 GB);
 //   * commit: the new energy of every leaf cell back into U.
 // Arithmetic is FP64 for both state precisions and follows the written
 // order (no contraction); divisions by the cell size are multiplications by

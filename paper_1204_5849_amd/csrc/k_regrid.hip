@@ -120,8 +120,8 @@ __global__ void __launch_bounds__(NTE) k_estimate2(EstArgs a)
 // through five source offsets formed once per block (below, inside and above
 // it), one plane ahead, so a block is read once and the cells cost no index
 // arithmetic; one barrier per plane, and 4.4 GB fetched for a 6.3 GB state
-// (two criteria; it was 6.9).  2764 -> 1472 us for 22016 FP32 blocks, 771 ->
-// 441 for 5440 FP64 ones and 247 -> 165 for 1024 FP32 ones.  Bound by the
+// (two criteria; it was 6.9).  2656 -> 1475 us for 22016 FP32 blocks, 722 ->
+// 406 for 5440 FP64 ones and 117 -> 74 for 1000 FP32 ones.  Bound by the
 // march: a plane's loads, FP64 criteria and barrier for 256 cells.
 template <typename T, int NC>
 __global__ void __launch_bounds__(NTE3) k_estimate3(EstArgs a)

@@ -28,17 +28,19 @@
 // registers.
 //
 // What bounds it: issue on the three SIMDs that hold a ring wave, and the
-// waits at the barriers (waves wait 0.47 of their time; LDS bank conflicts, 8
-// times more with a wave on four adjacent rows, cost 0.04).  Against one thread per column for all
-// dimensions (two 4-wave workgroups per CU, 256 registers, 44 to 180 bytes of
-// them in scratch), per map_step on the Harris sheet with 4768 leaves: LF 1453
-// -> 1371 us, LF with HLLC 1664 -> 1430, WENO 4675 -> 3526, WENO with HLLC
-// 5077 -> 3620 (both stages with the fill between); the blast's 1464 leaves,
-// which had no spills, 423 -> 434 (412 at the other priorities).  Every sum and
-// contraction is the one-thread version's, so that the state and the FP64 time
-// steps taken from it keep their bits: scaling the half-step differences and
-// sources before they meet was 1 % faster, the face states of WENO from
-// differences (u0 + d/2) 7 %, but both moved the time steps, by up to 1e-7.
+// waits at the barriers (19328 leaves, LF: waves wait 0.50 of their time; LDS
+// bank conflicts, 8 times more with a wave on four adjacent rows, take 0.03 of
+// the LDS cycles).  Against one thread per column for all dimensions (two
+// 4-wave workgroups per CU, 256 registers, 44 to 180 bytes of them in scratch),
+// per map_step at the default step_shape 0: the Harris sheet's 4768 leaves, LF
+// 1489 -> 1385 us, LF with HLLC 1686 -> 1442, WENO 4744 -> 3571, WENO with HLLC
+// 5148 -> 3898 (both stages with the fill between); the blast's 1464 leaves,
+// without resistivity and spills, 429 -> 418 (416 at the priorities of shape
+// 1).  Every sum and contraction is the one-thread version's, so that the state
+// and the FP64 time steps taken from it keep their bits: scaling the half-step
+// differences and sources before they meet was 1 % faster, the face states of
+// WENO from differences (u0 + d/2) 7 %, but both moved the time steps, by up to
+// 1e-7.
 // The waves of one role run their own loop; every wave passes the same
 // barriers.  Ghost cells are read where the ghost descriptors point (Sec.
 // 4.3), so U_out must not alias U_in (WENO stage 2 reads U_base at the cells

@@ -12,12 +12,12 @@
 // iteration; the blocks that would leave the last round of workgroups nearly
 // empty are cut into segments along z, each of which passes over the planes
 // next to it as well (without their x and y faces): 288 FP64
-// leaves on 256 CUs took two full rounds, 568 us, and take 337.
+// leaves on 256 CUs took two full rounds, 586 us (van Leer), and take 345.
 // Bound by instruction issue and LDS reads on one (FP64) or two (FP32) waves
-// per SIMD with ten barriers a plane.  Thread t owns the interior column (t % 16, t / 16); lanes 0-15
-// of wave w also own the ring cell of side w (x = -1, x = 16, y = -1,
-// y = 16) and lanes 16-35 the outer cells of the padded plane, as in the LF
-// kernel.  Per plane p:
+// per SIMD with ten barriers a plane.  Thread t owns the interior column
+// (t % 16, t / 16); lanes 0-15 of wave w also own the ring cell of side w (x =
+// -1, x = 16, y = -1, y = 16) and lanes 16-35 the outer cells of the padded
+// plane, as in the FP64 LF kernel.  Per plane p:
 //   * u(p) is published to LDS; the in-plane split fluxes F_x(u), F_y(u) of
 //     the whole padded plane are formed into one LDS buffer, one dimension
 //     at a time, and give the x and y terms of u~(p) on the interior and
