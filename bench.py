@@ -101,9 +101,10 @@ WENO_FLOPS_PER_CELL = {(3, True): (1723, 1742), (3, False): (1648, 1667),
 # flux 24, psi flux 1 -> 263 against 148 for Rusanov: 115 more per face.
 HLLC_EXTRA_PER_FACE = 115
 
-# MI355X vector peak for FP32 (non-packed) and FP64: 256 CUs x 4 SIMDs x
-# 16 lanes x 2 (FMA) x 2.4 GHz = 78.6 TFLOP/s
-ALU_PEAK_TFLOPS = 78.6
+# MI355X vector peaks: 256 CUs x 4 SIMDs x 64 lanes x 2 (FMA) x 2.4 GHz over the
+# cycles between two instructions of a SIMD, measured with two or more waves on
+# it: 2 for a (non-packed) FP32 add, multiply or FMA, 4 for an FP64 one
+ALU_PEAK_TFLOPS = {"fp32": 157.3, "fp64": 78.6}
 
 
 def step_sources_hash():
@@ -425,7 +426,8 @@ def config_roofline(wl, sim, precision):
     if fpc is not None:
         tflops = fpc * cells / ms * 1e-9
         r.update({"flops_per_cell_update": fpc, "alu_achieved_TFLOPs": tflops,
-                  "alu_peak_TFLOPs": ALU_PEAK_TFLOPS, "alu_frac": tflops / ALU_PEAK_TFLOPS})
+                  "alu_peak_TFLOPs": ALU_PEAK_TFLOPS[precision],
+                  "alu_frac": tflops / ALU_PEAK_TFLOPS[precision]})
     r["bound"] = "alu" if fpc is not None and r["alu_frac"] > r["hbm_frac"] else "hbm"
     return r
 
@@ -744,9 +746,9 @@ def main():
                    "limiter": wl.limiter, "glm": wl.glm_mode, "eta": wl.eta,
                    "state": args.precision, "launch": launch_label(chosen, args.eager),
                    "launch_config": chosen},
-        "roofline": {"bound": "alu", "achieved": tflops, "peak": ALU_PEAK_TFLOPS,
-                     "unit": "TFLOP/s", "frac": tflops / ALU_PEAK_TFLOPS, "traffic": traffic,
-                     "valu_busy": valu_busy,
+        "roofline": {"bound": "alu", "achieved": tflops, "peak": ALU_PEAK_TFLOPS[args.precision],
+                     "unit": "TFLOP/s", "frac": tflops / ALU_PEAK_TFLOPS[args.precision],
+                     "traffic": traffic, "valu_busy": valu_busy,
                      "kernel": "k_step3 (LF)" if wl.ndim == 3 else "k_step2 (LF)",
                      "kernel_ms": t_step * 1e3,
                      "flops_per_cell_update": fpc, "algorithmic_bytes_per_launch": bytes_step,
